@@ -26,30 +26,327 @@ constexpr int kHid = 64;
 constexpr int kFeat = HF_MLP_FEATURES;
 
 // ------------------------------------------------------------------ kernels
-// Z[i][j] = b[j] + sum_k X[i][k] W[k][j];  H = relu(Z) when H != nullptr.
-__global__ void __launch_bounds__(256) k_lin_fwd(const float* __restrict__ X, int n, int din,
-                                                 const float* __restrict__ W, const float* __restrict__ b,
-                                                 int dout, float* __restrict__ Z, float* __restrict__ H) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * dout) return;
-  const int i = t / dout, j = t - (t / dout) * dout;
-  float acc = b[j];
-  const float* x = X + (size_t)i * din;
-  for (int k = 0; k < din; ++k) acc = __builtin_fmaf(x[k], W[k * dout + j], acc);
-  Z[t] = acc;
-  if (H) H[t] = fmaxf(acc, 0.f);
+// One training step of every member of an ensemble is two launches:
+//   k_rows   everything that is local to a sample: the forward pass, the
+//            squared error's derivative and the chain of dz back to layer 1;
+//   k_grads  everything that sums over the samples: the gradient of each
+//            parameter, and its Adam update.
+// The second dimension of both grids is the member.  The sums keep one order:
+// a dot product over a layer's inputs runs from the bias (or 0) through the
+// inputs in order, a gradient through the samples in order, each in one lane
+// with fused multiply-adds, so results do not depend on the launch shape.
+//
+// What bounds a step is not arithmetic (0.5 GFLOP at 1500 samples and five
+// members) but the serial chain over the samples and the launches.  Thirteen
+// launches per member and step with one lane walking memory per output took
+// 1.43 ms per step of five members at 1500 samples and 42 features.
+
+// Rows of one sample tile, in LDS: [kRows][64] activations or dz of each wave.
+constexpr int kRows = 4;       // samples per wavefront (one float4 of a transposed row)
+constexpr int kRowWaves = 4;   // wavefronts per workgroup
+constexpr int kPad = kHid + 1;  // row pitch of a weight matrix in LDS: a column
+                                // and a row are both read without bank conflicts
+
+struct MlpArgs {
+  const float* X;   // [n][d] standardised samples
+  const float* Xt;  // [d][ns] the same, transposed
+  const float* y;   // [n]
+  float* p;         // [members][np] parameters
+  float* g;         // [members][np] gradients (k_grads without an update)
+  float* m;         // [members][np] Adam's moments
+  float* v;
+  float* ws;        // [members][wstride] workspace, see the offsets below
+  size_t wstride;
+  int n, ns, d, np;  // ns: pitch of a row of samples (pitch())
+  __host__ __device__ size_t o_ht(int l) const { return (size_t)l * kHid * ns; }          // [64][ns] layer l's output
+  __host__ __device__ size_t o_dz(int l) const { return (size_t)(3 + l) * kHid * ns; }    // [ns][64] its dz
+  __host__ __device__ size_t o_yh() const { return (size_t)6 * kHid * ns; }               // [ns] output
+  __host__ __device__ size_t o_d4() const { return (size_t)6 * kHid * ns + ns; }          // [ns] its dz
+  __host__ __device__ static size_t stride(int ns) { return (size_t)6 * kHid * ns + 2 * (size_t)ns; }
+  // k_grads requests up to 128 samples past the last one it uses
+  __host__ __device__ static int pitch(int n) { return (n + 63) / 64 * 64 + 128; }
+};
+
+// acc[r] += sum_k in[r][k] * w[k*wk], k in order.  `in` are kRows rows of 64 in
+// LDS (read as broadcasts), w this lane's column (wk = kPad) or row (wk = 1).
+__device__ __forceinline__ void dense64(const float* in, const float* w, int wk, float (&acc)[kRows]) {
+#pragma unroll 4
+  for (int k = 0; k < kHid; k += 4) {
+    float4 x[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) x[r] = *reinterpret_cast<const float4*>(in + r * kHid + k);
+    const float w0 = w[k * wk], w1 = w[(k + 1) * wk], w2 = w[(k + 2) * wk], w3 = w[(k + 3) * wk];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(x[r].x, w0, acc[r]);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(x[r].y, w1, acc[r]);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(x[r].z, w2, acc[r]);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(x[r].w, w3, acc[r]);
+  }
 }
 
-// dz[i] = (2/n)(yhat[i] - y[i]);  loss[0] = (1/n) sum (yhat - y)^2.  One
-// workgroup of 1024 lanes: strided partial sums, then a fixed LDS tree.
-__global__ void __launch_bounds__(1024) k_mse(const float* __restrict__ yhat, const float* __restrict__ y,
-                                              int n, float* __restrict__ dz, float* __restrict__ loss) {
+// Lane j of a wavefront holds output j of kRows samples.  The two 64x64
+// matrices sit in LDS, shared by the workgroup's wavefronts; the samples' rows
+// pass from layer to layer through LDS.  A wavefront past the last sample
+// repeats it and stores nothing.  TRAIN: also the dz of every layer.
+template <bool TRAIN>
+__global__ void __launch_bounds__(64 * kRowWaves) k_rows(MlpArgs a) {
+  __shared__ float w2[kHid * kPad], w3[kHid * kPad], w4[kHid];
+  __shared__ __align__(16) float rows[kRowWaves][kRows * kHid];
+  const int lane = (int)threadIdx.x & 63;
+  const int wave = (int)uniform(threadIdx.x >> 6);
+  const float* W1 = a.p + (size_t)blockIdx.y * a.np;
+  const float* b1 = W1 + (size_t)a.d * kHid;
+  const float* W2 = b1 + kHid;
+  const float* b2 = W2 + kHid * kHid;
+  const float* W3 = b2 + kHid;
+  const float* b3 = W3 + kHid * kHid;
+  const float* W4 = b3 + kHid;
+  const float* b4 = W4 + kHid;
+  float* ws = a.ws + (size_t)blockIdx.y * a.wstride;
+  float* in = rows[wave];
+  const int i0 = ((int)blockIdx.x * kRowWaves + wave) * kRows;
+
+  // both matrices are requested before layer 1 and put into LDS after it
+  constexpr int kLoads = kHid * kHid / (64 * kRowWaves);
+  float q2[kLoads], q3[kLoads];
+#pragma unroll
+  for (int t = 0; t < kLoads; ++t) {
+    q2[t] = W2[(int)threadIdx.x + 64 * kRowWaves * t];
+    q3[t] = W3[(int)threadIdx.x + 64 * kRowWaves * t];
+  }
+  const float q4 = W4[lane], bias2 = b2[lane], bias3 = b3[lane], bias4 = b4[0];
+  float acc[kRows], target[kRows];
+  const float* x[kRows];
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) {
+    const int i = min(i0 + r, a.n - 1);
+    x[r] = a.X + (size_t)i * a.d;
+    if (TRAIN) target[r] = a.y[i];
+    acc[r] = b1[lane];
+  }
+#pragma unroll 8
+  for (int k = 0; k < a.d; ++k) {
+    const float w = W1[(size_t)k * kHid + lane];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(x[r][k], w, acc[r]);
+  }
+#pragma unroll
+  for (int t = 0; t < kLoads; ++t) {
+    const int e = (int)threadIdx.x + 64 * kRowWaves * t;
+    w2[(e >> 6) * kPad + (e & 63)] = q2[t];
+    w3[(e >> 6) * kPad + (e & 63)] = q3[t];
+  }
+  if (wave == 0) w4[lane] = q4;
+
+  float h[3][kRows];
+  auto keep = [&](int l) {  // layer l's output: to LDS for the next layer, transposed to memory
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      h[l][r] = fmaxf(acc[r], 0.f);
+      in[r * kHid + lane] = h[l][r];
+    }
+    if (TRAIN && i0 < a.n)  // rows past n lie within the pitch and are not read
+      *reinterpret_cast<float4*>(ws + a.o_ht(l) + (size_t)lane * a.ns + i0) =
+          make_float4(h[l][0], h[l][1], h[l][2], h[l][3]);
+    __syncthreads();
+  };
+  keep(0);
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) acc[r] = bias2;
+  dense64(in, w2 + lane, kPad, acc);
+  __syncthreads();
+  keep(1);
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) acc[r] = bias3;
+  dense64(in, w3 + lane, kPad, acc);
+  __syncthreads();
+  keep(2);
+  // the output, the same in every lane
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) acc[r] = bias4;
+  dense64(in, w4, 1, acc);
+  float d4[kRows];
+  const float inv = 1.0f / (float)a.n;
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) {
+    const int i = i0 + r;
+    if (lane == 0 && i < a.n) ws[a.o_yh() + i] = acc[r];
+    if (TRAIN) {
+      const float e = acc[r] - target[r];
+      d4[r] = 2.0f * e * inv;
+      if (lane == 0 && i < a.n) ws[a.o_d4() + i] = d4[r];
+    }
+  }
+  if constexpr (TRAIN) {
+    auto send = [&](int l, float (&dz)[kRows]) {  // dz of layer l: to memory and to LDS
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        dz[r] = h[l][r] > 0.f ? dz[r] : 0.f;
+        in[r * kHid + lane] = dz[r];
+        if (i0 + r < a.n) ws[a.o_dz(l) + (size_t)(i0 + r) * kHid + lane] = dz[r];
+      }
+      __syncthreads();
+    };
+    float dz[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) dz[r] = __builtin_fmaf(d4[r], q4, 0.f);
+    send(2, dz);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) dz[r] = 0.f;
+    dense64(in, w3 + lane * kPad, 1, dz);
+    send(1, dz);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) dz[r] = 0.f;
+    dense64(in, w2 + lane * kPad, 1, dz);
+    send(0, dz);
+  }
+}
+
+// dW[k][j] = sum_i A[i][k] dZ[i][j] and db[j] = sum_i dZ[i][j], samples in
+// order, then (UPDATE) Adam on the parameter.  A wavefront takes two rows k of
+// one layer (the bias is the row after the last, with A = 1), lane j the column:
+// the two chains share one read of dZ's row, and a chain's latency (not the
+// arithmetic) is what a wavefront waits for, so dZ is requested kAhead rows
+// early into a second set of registers.  A's values come transposed, a tile of
+// them into LDS, from where four samples are read at once.  The output layer
+// has one column, so its lanes are the rows and A and dZ change places: d4 is
+// the broadcast value and the walk goes along h3; its bias walks d4 itself.
+constexpr int kTile = 1024;  // samples of A in LDS
+constexpr int kAhead = 32;   // rows of dZ requested together
+
+struct AdamArgs {
+  float lr, b1, b2, eps, bc1, bc2;  // bias corrections bc1 = 1 - b1^t, bc2 = 1 - b2^t
+};
+
+__host__ __device__ constexpr int grad_jobs(int d) { return (d + 2) / 2 + 2 * ((kHid + 2) / 2) + 2; }
+
+// s0 += sum_i A0[i] * col[i * STEP], s1 likewise with A1; a null A is all ones.
+template <int STEP>
+__device__ __forceinline__ void chains(float (&A)[2][kTile], const float* r0, const float* r1, const float* col, int n,
+                                       int lane, float& s0, float& s1) {
+  for (int t0 = 0; t0 < n; t0 += kTile) {
+    const int cnt = min(kTile, n - t0);
+    __syncthreads();
+    for (int i = lane; i < cnt; i += 64) {
+      A[0][i] = r0 ? r0[t0 + i] : 1.f;
+      A[1][i] = r1 ? r1[t0 + i] : 1.f;
+    }
+    __syncthreads();
+    const float* c = col + (size_t)t0 * STEP;
+    auto run = [&](int i, const float (&b)[kAhead]) {
+#pragma unroll
+      for (int u = 0; u < kAhead; u += 4) {
+        const float4 a0 = *reinterpret_cast<const float4*>(&A[0][i + u]);
+        const float4 a1 = *reinterpret_cast<const float4*>(&A[1][i + u]);
+        s0 = __builtin_fmaf(a0.x, b[u], s0);
+        s1 = __builtin_fmaf(a1.x, b[u], s1);
+        s0 = __builtin_fmaf(a0.y, b[u + 1], s0);
+        s1 = __builtin_fmaf(a1.y, b[u + 1], s1);
+        s0 = __builtin_fmaf(a0.z, b[u + 2], s0);
+        s1 = __builtin_fmaf(a1.z, b[u + 2], s1);
+        s0 = __builtin_fmaf(a0.w, b[u + 3], s0);
+        s1 = __builtin_fmaf(a1.w, b[u + 3], s1);
+      }
+    };
+    float ba[kAhead], bb[kAhead];
+    auto load = [&](int i, float (&b)[kAhead]) {  // samples past the last lie within the pitch
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) b[u] = c[(size_t)(i + u) * STEP];
+    };
+    int i = 0;
+    load(0, ba);
+    load(kAhead, bb);
+    for (; i + 2 * kAhead <= cnt; i += 2 * kAhead) {
+      run(i, ba);
+      load(i + 2 * kAhead, ba);
+      run(i + kAhead, bb);
+      load(i + 3 * kAhead, bb);
+    }
+    if (i + kAhead <= cnt) {
+      run(i, ba);
+      i += kAhead;
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) ba[u] = bb[u];
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (i + u < cnt) {
+        s0 = __builtin_fmaf(A[0][i + u], ba[u], s0);
+        s1 = __builtin_fmaf(A[1][i + u], ba[u], s1);
+      }
+  }
+}
+
+template <bool UPDATE>
+__global__ void __launch_bounds__(64) k_grads(MlpArgs a, AdamArgs ad) {
+  __shared__ __align__(16) float A[2][kTile];
+  const int lane = (int)threadIdx.x;
+  const float* ws = a.ws + (size_t)blockIdx.y * a.wstride;
+  size_t off = (size_t)blockIdx.y * a.np;  // of this workgroup's layer
+  const int j1 = (a.d + 2) / 2, j2 = (kHid + 2) / 2;
+  int job = (int)blockIdx.x;
+  auto put = [&](size_t t, float gi) {
+    if constexpr (UPDATE) {
+      const float mi = ad.b1 * a.m[t] + (1.f - ad.b1) * gi;
+      const float vi = ad.b2 * a.v[t] + (1.f - ad.b2) * gi * gi;
+      a.m[t] = mi;
+      a.v[t] = vi;
+      a.p[t] = a.p[t] - ad.lr * (mi / ad.bc1) / (sqrtf(vi / ad.bc2) + ad.eps);
+    } else {
+      a.g[t] = gi;
+    }
+  };
+  float s0 = 0.f, s1 = 0.f;
+  if (job < j1 + 2 * j2) {
+    int din = a.d;
+    const float *at = a.Xt, *dz = ws + a.o_dz(0);
+    if (job >= j1) {
+      const int l = 1 + (job - j1) / j2;
+      job = (job - j1) % j2;
+      din = kHid;
+      off += (size_t)a.d * kHid + kHid + (size_t)(l - 1) * (kHid * kHid + kHid);
+      at = ws + a.o_ht(l - 1);
+      dz = ws + a.o_dz(l);
+    }
+    const int k0 = 2 * job, k1 = 2 * job + 1;
+    chains<kHid>(A, k0 < din ? at + (size_t)k0 * a.ns : nullptr, k1 < din ? at + (size_t)k1 * a.ns : nullptr, dz + lane,
+                 a.n, lane, s0, s1);
+    put(off + (size_t)k0 * kHid + lane, s0);
+    if (k1 <= din) put(off + (size_t)k1 * kHid + lane, s1);
+  } else {
+    off += (size_t)a.d * kHid + kHid + 2 * (kHid * kHid + kHid);
+    const float* d4 = ws + a.o_d4();
+    if (job == j1 + 2 * j2) {
+      chains<1>(A, d4, d4, ws + a.o_ht(2) + (size_t)lane * a.ns, a.n, lane, s0, s1);
+      put(off + lane, s0);
+    } else {
+      chains<1>(A, nullptr, nullptr, d4, a.n, lane, s0, s1);
+      if (lane == 0) put(off + kHid, s0);
+    }
+  }
+}
+
+// Xt[k][i] = X[i][k]: lanes along the samples, so the stores are whole lines.
+__global__ void __launch_bounds__(256) k_transpose(const float* __restrict__ X, int n, int ns, int d,
+                                                   float* __restrict__ Xt) {
+  const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (i < n)
+    for (int k = (int)blockIdx.y; k < d; k += (int)gridDim.y) Xt[(size_t)k * ns + i] = X[(size_t)i * d + k];
+}
+
+// loss[member] = (1/n) sum (yhat - y)^2.  One workgroup of 1024 lanes per
+// member: strided partial sums, then a fixed LDS tree.
+__global__ void __launch_bounds__(1024) k_loss(MlpArgs a, float* __restrict__ loss) {
   __shared__ float red[1024];
+  const float* yhat = a.ws + (size_t)blockIdx.x * a.wstride + a.o_yh();
   float s = 0.f;
-  const float inv = 1.0f / (float)n;
-  for (int i = threadIdx.x; i < n; i += 1024) {
-    const float e = yhat[i] - y[i];
-    dz[i] = 2.0f * e * inv;
+  const float inv = 1.0f / (float)a.n;
+  for (int i = threadIdx.x; i < a.n; i += 1024) {
+    const float e = yhat[i] - a.y[i];
     s = __builtin_fmaf(e, e, s);
   }
   red[threadIdx.x] = s;
@@ -58,71 +355,21 @@ __global__ void __launch_bounds__(1024) k_mse(const float* __restrict__ yhat, co
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) loss[0] = red[0] * inv;
-}
-
-// dW[k][j] = sum_i A[i][k] dZ[i][j] (lanes t < din*dout);  db[j] = sum_i dZ[i][j]
-// (lanes din*dout + j).  Sequential over i in row order.
-__global__ void __launch_bounds__(256) k_lin_bwd_w(const float* __restrict__ A, const float* __restrict__ dZ,
-                                                   int n, int din, int dout, float* __restrict__ dW,
-                                                   float* __restrict__ db) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < din * dout) {
-    const int k = t / dout, j = t - (t / dout) * dout;
-    float acc = 0.f;
-    for (int i = 0; i < n; ++i) acc = __builtin_fmaf(A[(size_t)i * din + k], dZ[(size_t)i * dout + j], acc);
-    dW[t] = acc;
-  } else if (t < din * dout + dout) {
-    const int j = t - din * dout;
-    float acc = 0.f;
-    for (int i = 0; i < n; ++i) acc += dZ[(size_t)i * dout + j];
-    db[j] = acc;
-  }
-}
-
-// dZp[i][k] = (sum_j dZ[i][j] W[k][j]) * (Zp[i][k] > 0): the gradient through
-// the layer below and its ReLU.
-__global__ void __launch_bounds__(256) k_lin_bwd_x(const float* __restrict__ dZ, const float* __restrict__ W,
-                                                   const float* __restrict__ Zp, int n, int din, int dout,
-                                                   float* __restrict__ dZp) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * din) return;
-  const int i = t / din, k = t - (t / din) * din;
-  float acc = 0.f;
-  const float* dz = dZ + (size_t)i * dout;
-  const float* w = W + (size_t)k * dout;
-  for (int j = 0; j < dout; ++j) acc = __builtin_fmaf(dz[j], w[j], acc);
-  dZp[t] = Zp[t] > 0.f ? acc : 0.f;
-}
-
-// Adam with bias corrections bc1 = 1 - b1^t, bc2 = 1 - b2^t.
-__global__ void __launch_bounds__(256) k_adam(float* __restrict__ p, const float* __restrict__ g,
-                                              float* __restrict__ m, float* __restrict__ v, int np, float lr,
-                                              float b1, float b2, float eps, float bc1, float bc2) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= np) return;
-  const float gi = g[t];
-  const float mi = b1 * m[t] + (1.f - b1) * gi;
-  const float vi = b2 * v[t] + (1.f - b2) * gi * gi;
-  m[t] = mi;
-  v[t] = vi;
-  p[t] = p[t] - lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+  if (threadIdx.x == 0) loss[blockIdx.x] = red[0] * inv;
 }
 
 // ------------------------------------------------------------------ model state
-// An ensemble of `members` networks of the same shape, trained one after the
-// other on the same standardised data from different initial weights; the
-// prediction is the mean of the members' predictions.  p/m/v point at the
-// active member's slice of pall/mall/vall (use_member).
+// An ensemble of `members` networks of the same shape, trained side by side on
+// the same standardised data from different initial weights; the prediction is
+// the mean of the members' predictions.
 struct MlpModel {
-  int d = 0, np = 0, cap_n = 0, t = 0, members = 1;
+  int d = 0, np = 0, t = 0, members = 1;
   bool trained = false;
-  float *pall = nullptr, *mall = nullptr, *vall = nullptr;
-  float *p = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
-  // workspace
-  float *X = nullptr, *y = nullptr, *Z1 = nullptr, *H1 = nullptr, *Z2 = nullptr, *H2 = nullptr;
-  float *Z3 = nullptr, *H3 = nullptr, *yh = nullptr, *d4 = nullptr, *d3 = nullptr, *d2 = nullptr,
-        *d1 = nullptr, *loss = nullptr;
+  float *p = nullptr, *m = nullptr, *v = nullptr;  // [members][np] parameters and Adam's moments
+  float* g = nullptr;                              // [np] gradient of the first member
+  // workspace: one allocation for cap_n samples and `slots` members at a time
+  int cap_n = 0, slots = 0;
+  float *arena = nullptr, *X = nullptr, *Xt = nullptr, *y = nullptr, *loss = nullptr, *ws = nullptr;
   std::vector<float> mu, sd;
   float ymu = 0.f, ysd = 1.f;
 };
@@ -131,20 +378,9 @@ static MlpModel* g_model = nullptr;  // one model per process, on the device tha
 static int g_model_dev = -1;
 
 static void mlp_free_ws(MlpModel* M) {
-  float** ws[] = {&M->X, &M->y, &M->Z1, &M->H1, &M->Z2, &M->H2, &M->Z3, &M->H3,
-                  &M->yh, &M->d4, &M->d3, &M->d2, &M->d1, &M->loss};
-  for (float** q : ws)
-    if (*q) {
-      (void)hipFree(*q);
-      *q = nullptr;
-    }
-  M->cap_n = 0;
-}
-
-static void use_member(MlpModel* M, int k) {
-  M->p = M->pall + (size_t)k * M->np;
-  M->m = M->mall + (size_t)k * M->np;
-  M->v = M->vall + (size_t)k * M->np;
+  if (M->arena) (void)hipFree(M->arena);
+  M->arena = nullptr;
+  M->cap_n = M->slots = 0;
 }
 
 void mlp_free() {
@@ -153,9 +389,7 @@ void mlp_free() {
   (void)hipGetDevice(&cur);
   (void)hipSetDevice(g_model_dev);
   mlp_free_ws(g_model);
-  float** ps[] = {&g_model->pall, &g_model->mall, &g_model->vall, &g_model->g};
-  for (float** q : ps)
-    if (*q) (void)hipFree(*q);
+  if (g_model->p) (void)hipFree(g_model->p);  // with the moments and the gradient
   delete g_model;
   g_model = nullptr;
   (void)hipSetDevice(cur);
@@ -172,19 +406,28 @@ static int alloc_f(float** q, size_t n) {
   return HF_OK;
 }
 
+// Members whose samples are in flight together: all of them, unless that takes
+// more than 256 MiB of workspace.
+static int slots_for(int members, int n) {
+  const size_t one = MlpArgs::stride(MlpArgs::pitch(n)) * sizeof(float);
+  return (int)std::max<size_t>(1, std::min<size_t>((size_t)members, (size_t(256) << 20) / one));
+}
+
 static int ensure_ws(MlpModel* M, int n) {
   if (n <= M->cap_n) return HF_OK;
   mlp_free_ws(M);
-  const int c = std::max(n, 1024);
+  const int c = std::max(n, 1024), slots = slots_for(M->members, c);
+  const size_t ns = MlpArgs::pitch(c);
+  const size_t fx = ((size_t)c * M->d + 63) / 64 * 64, fxt = ns * M->d, fy = ns, fl = 64;
   int rc;
-  if ((rc = alloc_f(&M->X, (size_t)c * M->d)) || (rc = alloc_f(&M->y, c)) || (rc = alloc_f(&M->Z1, (size_t)c * kHid)) ||
-      (rc = alloc_f(&M->H1, (size_t)c * kHid)) || (rc = alloc_f(&M->Z2, (size_t)c * kHid)) ||
-      (rc = alloc_f(&M->H2, (size_t)c * kHid)) || (rc = alloc_f(&M->Z3, (size_t)c * kHid)) ||
-      (rc = alloc_f(&M->H3, (size_t)c * kHid)) || (rc = alloc_f(&M->yh, c)) || (rc = alloc_f(&M->d4, c)) ||
-      (rc = alloc_f(&M->d3, (size_t)c * kHid)) || (rc = alloc_f(&M->d2, (size_t)c * kHid)) ||
-      (rc = alloc_f(&M->d1, (size_t)c * kHid)) || (rc = alloc_f(&M->loss, 1)))
-    return rc;
+  if ((rc = alloc_f(&M->arena, fx + fxt + fy + fl + (size_t)slots * MlpArgs::stride((int)ns))) != HF_OK) return rc;
+  M->X = M->arena;
+  M->Xt = M->X + fx;
+  M->y = M->Xt + fxt;
+  M->loss = M->y + fy;
+  M->ws = M->loss + fl;
   M->cap_n = c;
+  M->slots = slots;
   return HF_OK;
 }
 
@@ -198,8 +441,6 @@ static int model(MlpModel** out) {
   return HF_OK;
 }
 
-static int blocks_for(int n) { return std::max(1, (n + 255) / 256); }
-
 #define HF_LAUNCH(...)                                  \
   do {                                                  \
     hipLaunchKernelGGL(__VA_ARGS__);                    \
@@ -207,54 +448,42 @@ static int blocks_for(int n) { return std::max(1, (n + 255) / 256); }
     if (e_ != hipSuccess) return record_hip(e_);        \
   } while (0)
 
-// Forward on M->X[n][d] (standardised); fills Z*, H*, yh.
-static int forward(MlpModel* M, int n, hipStream_t st) {
-  const float* W1 = M->p;
-  const float* b1 = W1 + M->d * kHid;
-  const float* W2 = b1 + kHid;
-  const float* b2 = W2 + kHid * kHid;
-  const float* W3 = b2 + kHid;
-  const float* b3 = W3 + kHid * kHid;
-  const float* W4 = b3 + kHid;
-  const float* b4 = W4 + kHid;
-  HF_LAUNCH(k_lin_fwd, dim3(blocks_for(n * kHid)), dim3(256), 0, st, M->X, n, M->d, W1, b1, kHid, M->Z1, M->H1);
-  HF_LAUNCH(k_lin_fwd, dim3(blocks_for(n * kHid)), dim3(256), 0, st, M->H1, n, kHid, W2, b2, kHid, M->Z2, M->H2);
-  HF_LAUNCH(k_lin_fwd, dim3(blocks_for(n * kHid)), dim3(256), 0, st, M->H2, n, kHid, W3, b3, kHid, M->Z3, M->H3);
-  HF_LAUNCH(k_lin_fwd, dim3(blocks_for(n)), dim3(256), 0, st, M->H3, n, kHid, W4, b4, 1, M->yh, (float*)nullptr);
+// Kernel arguments for members k .. on n samples (the pitch is that of n, not
+// of the workspace's capacity, so that it only depends on the call).
+static MlpArgs mlp_args(const MlpModel* M, int k, int n) {
+  const int ns = MlpArgs::pitch(n);
+  const size_t o = (size_t)k * M->np;
+  return MlpArgs{M->X, M->Xt, M->y, M->p + o, M->g, M->m + o, M->v + o, M->ws, MlpArgs::stride(ns), n, ns, M->d, M->np};
+}
+
+// Outputs of `cnt` members (and, TRAIN, every dz) for the samples in M->X.
+template <bool TRAIN>
+static int rows(const MlpArgs& a, int cnt, hipStream_t st) {
+  const int per = kRows * kRowWaves;
+  HF_LAUNCH(k_rows<TRAIN>, dim3((a.n + per - 1) / per, cnt), dim3(64 * kRowWaves), 0, st, a);
   return HF_OK;
 }
 
-// Loss and full gradient into M->g (forward must have run on the same X).
-static int backward(MlpModel* M, int n, hipStream_t st) {
-  const int d = M->d;
-  float* gW1 = M->g;
-  float* gb1 = gW1 + d * kHid;
-  float* gW2 = gb1 + kHid;
-  float* gb2 = gW2 + kHid * kHid;
-  float* gW3 = gb2 + kHid;
-  float* gb3 = gW3 + kHid * kHid;
-  float* gW4 = gb3 + kHid;
-  float* gb4 = gW4 + kHid;
-  const float* W2 = M->p + d * kHid + kHid;
-  const float* W3 = W2 + kHid * kHid + kHid;
-  const float* W4 = W3 + kHid * kHid + kHid;
-  HF_LAUNCH(k_mse, dim3(1), dim3(1024), 0, st, M->yh, M->y, n, M->d4, M->loss);
-  HF_LAUNCH(k_lin_bwd_w, dim3(blocks_for(kHid + 1)), dim3(256), 0, st, M->H3, M->d4, n, kHid, 1, gW4, gb4);
-  HF_LAUNCH(k_lin_bwd_x, dim3(blocks_for(n * kHid)), dim3(256), 0, st, M->d4, W4, M->Z3, n, kHid, 1, M->d3);
-  HF_LAUNCH(k_lin_bwd_w, dim3(blocks_for(kHid * kHid + kHid)), dim3(256), 0, st, M->H2, M->d3, n, kHid, kHid, gW3, gb3);
-  HF_LAUNCH(k_lin_bwd_x, dim3(blocks_for(n * kHid)), dim3(256), 0, st, M->d3, W3, M->Z2, n, kHid, kHid, M->d2);
-  HF_LAUNCH(k_lin_bwd_w, dim3(blocks_for(kHid * kHid + kHid)), dim3(256), 0, st, M->H1, M->d2, n, kHid, kHid, gW2, gb2);
-  HF_LAUNCH(k_lin_bwd_x, dim3(blocks_for(n * kHid)), dim3(256), 0, st, M->d2, W2, M->Z1, n, kHid, kHid, M->d1);
-  HF_LAUNCH(k_lin_bwd_w, dim3(blocks_for(d * kHid + kHid)), dim3(256), 0, st, M->X, M->d1, n, d, kHid, gW1, gb1);
+static int transpose(const MlpArgs& a, const MlpModel* M, hipStream_t st) {
+  HF_LAUNCH(k_transpose, dim3((a.n + 255) / 256, std::min(a.d, 64)), dim3(256), 0, st, M->X, a.n, a.ns, a.d, M->Xt);
   return HF_OK;
 }
 
-static int adam(MlpModel* M, float lr, hipStream_t st) {
-  M->t += 1;
+static AdamArgs adam_args(int t, float lr) {
   const double b1 = 0.9, b2 = 0.999;
-  const float bc1 = (float)(1.0 - std::pow(b1, M->t)), bc2 = (float)(1.0 - std::pow(b2, M->t));
-  HF_LAUNCH(k_adam, dim3(blocks_for(M->np)), dim3(256), 0, st, M->p, M->g, M->m, M->v, M->np, lr, (float)b1,
-            (float)b2, 1e-8f, bc1, bc2);
+  return AdamArgs{lr, (float)b1, (float)b2, 1e-8f, (float)(1.0 - std::pow(b1, t)), (float)(1.0 - std::pow(b2, t))};
+}
+
+// One full-batch Adam step t of `cnt` members.
+static int train_step(const MlpArgs& a, int cnt, int t, float lr, hipStream_t st) {
+  int rc = rows<true>(a, cnt, st);
+  if (rc != HF_OK) return rc;
+  HF_LAUNCH(k_grads<true>, dim3(grad_jobs(a.d), cnt), dim3(64), 0, st, a, adam_args(t, lr));
+  return HF_OK;
+}
+
+static int losses(const MlpArgs& a, const MlpModel* M, int cnt, hipStream_t st) {
+  HF_LAUNCH(k_loss, dim3(cnt), dim3(1024), 0, st, a, M->loss);
   return HF_OK;
 }
 
@@ -455,18 +684,21 @@ static void standardise(const MlpModel* M, const float* X, int n, std::vector<fl
 static int predict(MlpModel* M, const float* X, int n, float* y, hipStream_t st) {
   int rc;
   if ((rc = ensure_ws(M, n)) != HF_OK) return rc;
-  std::vector<float> xs, yk(n);
+  std::vector<float> xs;
   standardise(M, X, n, &xs);
   if ((rc = upload(M->X, xs.data(), xs.size(), st)) != HF_OK) return rc;
   std::vector<double> acc(n, 0.0);
-  for (int k = 0; k < M->members; ++k) {
-    use_member(M, k);
-    if ((rc = forward(M, n, st)) != HF_OK) break;
-    if ((rc = download(yk.data(), M->yh, n, st)) != HF_OK) break;
-    for (int i = 0; i < n; ++i) acc[i] += yk[i];
+  std::vector<float> yk((size_t)M->slots * n);
+  for (int k = 0; k < M->members; k += M->slots) {
+    const int cnt = std::min(M->slots, M->members - k);
+    const MlpArgs a = mlp_args(M, k, n);
+    if ((rc = rows<false>(a, cnt, st)) != HF_OK) return rc;
+    hipError_t e = hipMemcpy2DAsync(yk.data(), n * sizeof(float), a.ws + a.o_yh(), a.wstride * sizeof(float),
+                                    n * sizeof(float), cnt, hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess) return record_hip(e);
+    for (int j = 0; j < cnt; ++j)
+      for (int i = 0; i < n; ++i) acc[i] += yk[(size_t)j * n + i];
   }
-  use_member(M, 0);
-  if (rc != HF_OK) return rc;
   for (int i = 0; i < n; ++i) y[i] = (float)(acc[i] / M->members) * M->ysd + M->ymu;
   return HF_OK;
 }
@@ -504,15 +736,13 @@ int hf_mlp_init_ensemble(int d_in, uint64_t seed, int members) {
   M->np = nparams(d_in);
   M->members = members;
   const size_t all = (size_t)members * M->np;
-  if ((rc = alloc_f(&M->pall, all)) || (rc = alloc_f(&M->mall, all)) || (rc = alloc_f(&M->vall, all)) ||
-      (rc = alloc_f(&M->g, M->np))) {
-    float** ps[] = {&M->pall, &M->mall, &M->vall, &M->g};
-    for (float** q : ps)
-      if (*q) (void)hipFree(*q);
+  if ((rc = alloc_f(&M->p, 3 * all + M->np)) != HF_OK) {
     delete M;
     return rc;
   }
-  use_member(M, 0);
+  M->m = M->p + all;
+  M->v = M->m + all;
+  M->g = M->v + all;
   // He-uniform weights U(-sqrt(6/fan_in), +sqrt(6/fan_in)), zero biases;
   // member k draws from the splitmix64 stream seeded with seed + k
   std::vector<float> host(all, 0.f);
@@ -533,10 +763,9 @@ int hf_mlp_init_ensemble(int d_in, uint64_t seed, int members) {
   M->sd.assign(d_in, 1.f);
   g_model = M;
   g_model_dev = s->device;
-  hipError_t e = hipMemcpy(M->pall, host.data(), host.size() * sizeof(float), hipMemcpyHostToDevice);
+  hipError_t e = hipMemcpy(M->p, host.data(), host.size() * sizeof(float), hipMemcpyHostToDevice);
   if (e != hipSuccess) return record_hip(e);
-  if ((e = hipMemset(M->mall, 0, all * sizeof(float))) != hipSuccess) return record_hip(e);
-  if ((e = hipMemset(M->vall, 0, all * sizeof(float))) != hipSuccess) return record_hip(e);
+  if ((e = hipMemset(M->m, 0, 2 * all * sizeof(float))) != hipSuccess) return record_hip(e);  // both moments
   return HF_OK;
 }
 
@@ -578,9 +807,12 @@ int hf_mlp_grad(const float* X, const float* y, int n, float* loss_out, float* g
   int rc = model(&M);
   if (rc != HF_OK) return rc;
   if ((rc = ensure_ws(M, n)) != HF_OK) return rc;
+  const MlpArgs a = mlp_args(M, 0, n);
   if ((rc = upload(M->X, X, (size_t)n * M->d, nullptr)) || (rc = upload(M->y, y, n, nullptr)) ||
-      (rc = forward(M, n, nullptr)) || (rc = backward(M, n, nullptr)))
+      (rc = transpose(a, M, nullptr)) || (rc = rows<true>(a, 1, nullptr)))
     return rc;
+  HF_LAUNCH(k_grads<false>, dim3(grad_jobs(a.d), 1), dim3(64), 0, nullptr, a, AdamArgs{});
+  if ((rc = losses(a, M, 1, nullptr)) != HF_OK) return rc;
   if ((rc = download(loss_out, M->loss, 1, nullptr)) != HF_OK) return rc;
   return download(grad_out, M->g, M->np, nullptr);
 }
@@ -591,9 +823,12 @@ int hf_mlp_step(const float* X, const float* y, int n, float lr, float* loss_out
   int rc = model(&M);
   if (rc != HF_OK) return rc;
   if ((rc = ensure_ws(M, n)) != HF_OK) return rc;
+  const MlpArgs a = mlp_args(M, 0, n);
   if ((rc = upload(M->X, X, (size_t)n * M->d, nullptr)) || (rc = upload(M->y, y, n, nullptr)) ||
-      (rc = forward(M, n, nullptr)) || (rc = backward(M, n, nullptr)) || (rc = adam(M, lr, nullptr)))
+      (rc = transpose(a, M, nullptr)) || (rc = train_step(a, 1, M->t + 1, lr, nullptr)))
     return rc;
+  M->t += 1;
+  if ((rc = losses(a, M, 1, nullptr)) != HF_OK) return rc;
   return loss_out ? download(loss_out, M->loss, 1, nullptr) : HF_OK;
 }
 
@@ -637,29 +872,26 @@ int hf_mlp_train(const float* X, const float* y, int n, int d, int epochs, float
   for (int i = 0; i < n; ++i) ys[i] = (y[i] - M->ymu) / M->ysd;
   if ((rc = ensure_ws(M, n)) != HF_OK) return rc;
   if ((rc = upload(M->X, xs.data(), xs.size(), nullptr)) || (rc = upload(M->y, ys.data(), n, nullptr))) return rc;
+  if ((rc = transpose(mlp_args(M, 0, n), M, nullptr)) != HF_OK) return rc;
   // every member from its own initial weights, on the same data
   double lsum = 0.0;
-  for (int k = 0; k < M->members; ++k) {
-    use_member(M, k);
-    M->t = 0;
-    hipError_t e;
-    if ((e = hipMemset(M->m, 0, M->np * sizeof(float))) != hipSuccess ||
-        (e = hipMemset(M->v, 0, M->np * sizeof(float))) != hipSuccess) {
-      use_member(M, 0);
-      return record_hip(e);
-    }
-    for (int ep = 0; ep < epochs && rc == HF_OK; ++ep)
-      if ((rc = forward(M, n, nullptr)) || (rc = backward(M, n, nullptr)) || (rc = adam(M, lr, nullptr))) break;
-    // loss of the member's final parameters
-    if (rc == HF_OK && ((rc = forward(M, n, nullptr)) == HF_OK) && ((rc = backward(M, n, nullptr)) == HF_OK)) {
-      float l = 0.f;
-      rc = download(&l, M->loss, 1, nullptr);
-      lsum += l;
-    }
-    if (rc != HF_OK) break;
+  M->t = 0;
+  const size_t all = (size_t)M->members * M->np;
+  hipError_t e = hipMemsetAsync(M->m, 0, 2 * all * sizeof(float), nullptr);  // both moments
+  if (e != hipSuccess) return record_hip(e);
+  for (int k = 0; k < M->members; k += M->slots) {
+    const int cnt = std::min(M->slots, M->members - k);
+    const MlpArgs a = mlp_args(M, k, n);
+    for (int ep = 1; ep <= epochs; ++ep)
+      if ((rc = train_step(a, cnt, ep, lr, nullptr)) != HF_OK) return rc;
+    // loss of the members' final parameters
+    float l[HF_MLP_MAX_MEMBERS];
+    if ((rc = rows<false>(a, cnt, nullptr)) || (rc = losses(a, M, cnt, nullptr)) ||
+        (rc = download(l, M->loss, cnt, nullptr)))
+      return rc;
+    for (int j = 0; j < cnt; ++j) lsum += l[j];
   }
-  use_member(M, 0);
-  if (rc != HF_OK) return rc;
+  M->t = epochs;
   if (loss_out) *loss_out = (float)(lsum / M->members);
   M->trained = true;
   return HF_OK;
@@ -680,7 +912,7 @@ int hf_mlp_save(const char* path) {
   if (!path) return HF_EINVAL;
   const size_t all = (size_t)M->members * M->np;
   std::vector<float> p(all);
-  if ((rc = download(p.data(), M->pall, all, nullptr)) != HF_OK) return rc;
+  if ((rc = download(p.data(), M->p, all, nullptr)) != HF_OK) return rc;
   FILE* f = std::fopen(path, "wb");
   if (!f) return HF_EINVAL;
   const char magic[8] = {'H', 'F', 'M', 'L', 'P', '2', 0, 0};
@@ -717,7 +949,7 @@ int hf_mlp_load(const char* path) {
   if (!ok) return HF_EINVAL;
   int rc = hf_mlp_init_ensemble(hdr[0], 0, hdr[3]);
   if (rc != HF_OK) return rc;
-  if ((rc = upload(g_model->pall, p.data(), all, nullptr)) != HF_OK) return rc;
+  if ((rc = upload(g_model->p, p.data(), all, nullptr)) != HF_OK) return rc;
   hipError_t e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) return record_hip(e);
   g_model->mu = mu;
