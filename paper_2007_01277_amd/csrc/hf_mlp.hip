@@ -39,11 +39,13 @@ constexpr int kFeat = HF_MLP_FEATURES;
 // What bounds a step is not arithmetic (0.5 GFLOP at 1500 samples and five
 // members) but the serial chain over the samples and the launches.  Thirteen
 // launches per member and step with one lane walking memory per output took
-// 1.43 ms per step of five members at 1500 samples and 42 features.
+// 7.2 ms per step of five members at 1500 samples and 42 features; the two
+// launches take 18 + 22 us for all five members.
 
 // Rows of one sample tile, in LDS: [kRows][64] activations or dz of each wave.
 constexpr int kRows = 4;       // samples per wavefront (one float4 of a transposed row)
 constexpr int kRowWaves = 4;   // wavefronts per workgroup
+constexpr int kTile = 128;     // samples of one step of k_grads
 constexpr int kPad = kHid + 1;  // row pitch of a weight matrix in LDS: a column
                                 // and a row are both read without bank conflicts
 
@@ -58,33 +60,59 @@ struct MlpArgs {
   float* ws;        // [members][wstride] workspace, see the offsets below
   size_t wstride;
   int n, ns, d, np;  // ns: pitch of a row of samples (pitch())
-  __host__ __device__ size_t o_ht(int l) const { return (size_t)l * kHid * ns; }          // [64][ns] layer l's output
+  __host__ __device__ size_t o_ht(int l) const { return (size_t)l * kHid * ns; }          // [64][ns] layer l < 2's output
   __host__ __device__ size_t o_dz(int l) const { return (size_t)(3 + l) * kHid * ns; }    // [ns][64] its dz
+  __host__ __device__ size_t o_h3() const { return (size_t)2 * kHid * ns; }               // [ns][64] layer 3's output
   __host__ __device__ size_t o_yh() const { return (size_t)6 * kHid * ns; }               // [ns] output
   __host__ __device__ size_t o_d4() const { return (size_t)6 * kHid * ns + ns; }          // [ns] its dz
   __host__ __device__ static size_t stride(int ns) { return (size_t)6 * kHid * ns + 2 * (size_t)ns; }
-  // k_grads requests up to 128 samples past the last one it uses
-  __host__ __device__ static int pitch(int n) { return (n + 63) / 64 * 64 + 128; }
+  // whole tiles of k_grads
+  __host__ __device__ static int pitch(int n) { return (n + kTile - 1) / kTile * kTile; }
 };
 
 // acc[r] += sum_k in[r][k] * w[k*wk], k in order.  `in` are kRows rows of 64 in
 // LDS (read as broadcasts), w this lane's column (wk = kPad) or row (wk = 1).
+// The next four inputs are read while these four are used; the loop stays
+// rolled, since every wavefront passes here only once per layer and straight-
+// line code is then bound by instruction fetch (fully unrolled: 27 us per
+// launch instead of 19).
 __device__ __forceinline__ void dense64(const float* in, const float* w, int wk, float (&acc)[kRows]) {
-#pragma unroll 4
-  for (int k = 0; k < kHid; k += 4) {
+  struct Step {
     float4 x[kRows];
+    float w[4];
+  };
+  auto load = [&](int k, Step& q) {
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) x[r] = *reinterpret_cast<const float4*>(in + r * kHid + k);
-    const float w0 = w[k * wk], w1 = w[(k + 1) * wk], w2 = w[(k + 2) * wk], w3 = w[(k + 3) * wk];
+    for (int r = 0; r < kRows; ++r) q.x[r] = *reinterpret_cast<const float4*>(in + r * kHid + k);
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(x[r].x, w0, acc[r]);
+    for (int c = 0; c < 4; ++c) q.w[c] = w[(k + c) * wk];
+  };
+  auto use = [&](const Step& q) {
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(x[r].y, w1, acc[r]);
+    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(q.x[r].x, q.w[0], acc[r]);
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(x[r].z, w2, acc[r]);
+    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(q.x[r].y, q.w[1], acc[r]);
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(x[r].w, w3, acc[r]);
+    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(q.x[r].z, q.w[2], acc[r]);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(q.x[r].w, q.w[3], acc[r]);
+  };
+  Step q[3];
+  load(0, q[0]);
+  load(4, q[1]);
+#pragma unroll 1
+  for (int k = 0; k < kHid - 4; k += 12) {  // 60 inputs, then the last four
+    load(k + 8, q[2]);
+    __builtin_amdgcn_sched_barrier(0);
+    use(q[0]);
+    load(k + 12, q[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    use(q[1]);
+    load(min(k + 16, kHid - 4), q[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    use(q[2]);
   }
+  use(q[0]);
 }
 
 // Lane j of a wavefront holds output j of kRows samples.  The two 64x64
@@ -148,7 +176,11 @@ __global__ void __launch_bounds__(64 * kRowWaves) k_rows(MlpArgs a) {
       h[l][r] = fmaxf(acc[r], 0.f);
       in[r * kHid + lane] = h[l][r];
     }
-    if (TRAIN && i0 < a.n)  // rows past n lie within the pitch and are not read
+    if (TRAIN && l == 2) {
+#pragma unroll
+      for (int r = 0; r < kRows; ++r)
+        if (i0 + r < a.n) ws[a.o_h3() + (size_t)(i0 + r) * kHid + lane] = h[l][r];
+    } else if (TRAIN && i0 < a.n)  // rows past n lie within the pitch and are not used
       *reinterpret_cast<float4*>(ws + a.o_ht(l) + (size_t)lane * a.ns + i0) =
           make_float4(h[l][0], h[l][1], h[l][2], h[l][3]);
     __syncthreads();
@@ -207,126 +239,115 @@ __global__ void __launch_bounds__(64 * kRowWaves) k_rows(MlpArgs a) {
 }
 
 // dW[k][j] = sum_i A[i][k] dZ[i][j] and db[j] = sum_i dZ[i][j], samples in
-// order, then (UPDATE) Adam on the parameter.  A wavefront takes two rows k of
-// one layer (the bias is the row after the last, with A = 1), lane j the column:
-// the two chains share one read of dZ's row, and a chain's latency (not the
-// arithmetic) is what a wavefront waits for, so dZ is requested kAhead rows
-// early into a second set of registers.  A's values come transposed, a tile of
-// them into LDS, from where four samples are read at once.  The output layer
-// has one column, so its lanes are the rows and A and dZ change places: d4 is
-// the broadcast value and the walk goes along h3; its bias walks d4 itself.
-constexpr int kTile = 1024;  // samples of A in LDS
-constexpr int kAhead = 32;   // rows of dZ requested together
-
+// order, then (UPDATE) Adam on the parameter.  A wavefront takes one row k of a
+// layer (the bias is the row after the last, with A = 1), lane j the column; a
+// workgroup's four rows share dZ, which passes through LDS in tiles of kTile
+// samples, the next tile requested before this one is used.  The samples were
+// written by other dies a moment ago, so a read takes about 1700 cycles to come
+// back: a tile's chain covers that, and sharing divides the traffic by four.  A
+// comes transposed, so four of its values are one (broadcast) LDS read.  (Two
+// rows per wavefront, reading dZ from memory 32 samples ahead: 33-35 us per
+// launch at 1500 samples and five members.)  The output layer has one column:
+// its lanes are the rows, d4 is the broadcast value and the tiles are of h3; its
+// bias, in the second wavefront, adds d4 alone.
 struct AdamArgs {
   float lr, b1, b2, eps, bc1, bc2;  // bias corrections bc1 = 1 - b1^t, bc2 = 1 - b2^t
 };
 
-__host__ __device__ constexpr int grad_jobs(int d) { return (d + 2) / 2 + 2 * ((kHid + 2) / 2) + 2; }
-
-// s0 += sum_i A0[i] * col[i * STEP], s1 likewise with A1; a null A is all ones.
-template <int STEP>
-__device__ __forceinline__ void chains(float (&A)[2][kTile], const float* r0, const float* r1, const float* col, int n,
-                                       int lane, float& s0, float& s1) {
-  for (int t0 = 0; t0 < n; t0 += kTile) {
-    const int cnt = min(kTile, n - t0);
-    __syncthreads();
-    for (int i = lane; i < cnt; i += 64) {
-      A[0][i] = r0 ? r0[t0 + i] : 1.f;
-      A[1][i] = r1 ? r1[t0 + i] : 1.f;
-    }
-    __syncthreads();
-    const float* c = col + (size_t)t0 * STEP;
-    auto run = [&](int i, const float (&b)[kAhead]) {
-#pragma unroll
-      for (int u = 0; u < kAhead; u += 4) {
-        const float4 a0 = *reinterpret_cast<const float4*>(&A[0][i + u]);
-        const float4 a1 = *reinterpret_cast<const float4*>(&A[1][i + u]);
-        s0 = __builtin_fmaf(a0.x, b[u], s0);
-        s1 = __builtin_fmaf(a1.x, b[u], s1);
-        s0 = __builtin_fmaf(a0.y, b[u + 1], s0);
-        s1 = __builtin_fmaf(a1.y, b[u + 1], s1);
-        s0 = __builtin_fmaf(a0.z, b[u + 2], s0);
-        s1 = __builtin_fmaf(a1.z, b[u + 2], s1);
-        s0 = __builtin_fmaf(a0.w, b[u + 3], s0);
-        s1 = __builtin_fmaf(a1.w, b[u + 3], s1);
-      }
-    };
-    float ba[kAhead], bb[kAhead];
-    auto load = [&](int i, float (&b)[kAhead]) {  // samples past the last lie within the pitch
-#pragma unroll
-      for (int u = 0; u < kAhead; ++u) b[u] = c[(size_t)(i + u) * STEP];
-    };
-    int i = 0;
-    load(0, ba);
-    load(kAhead, bb);
-    for (; i + 2 * kAhead <= cnt; i += 2 * kAhead) {
-      run(i, ba);
-      load(i + 2 * kAhead, ba);
-      run(i + kAhead, bb);
-      load(i + 3 * kAhead, bb);
-    }
-    if (i + kAhead <= cnt) {
-      run(i, ba);
-      i += kAhead;
-#pragma unroll
-      for (int u = 0; u < kAhead; ++u) ba[u] = bb[u];
-    }
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u)
-      if (i + u < cnt) {
-        s0 = __builtin_fmaf(A[0][i + u], ba[u], s0);
-        s1 = __builtin_fmaf(A[1][i + u], ba[u], s1);
-      }
-  }
-}
+constexpr int kGradRows = 4;  // rows (wavefronts) per workgroup
+__host__ __device__ constexpr int row_groups(int din) { return (din + kGradRows) / kGradRows; }  // din rows and the bias
+__host__ __device__ constexpr int grad_jobs(int d) { return row_groups(d) + 2 * row_groups(kHid) + 1; }
 
 template <bool UPDATE>
-__global__ void __launch_bounds__(64) k_grads(MlpArgs a, AdamArgs ad) {
-  __shared__ __align__(16) float A[2][kTile];
-  const int lane = (int)threadIdx.x;
+__global__ void __launch_bounds__(64 * kGradRows) k_grads(MlpArgs a, AdamArgs ad) {
+  constexpr int kQ = kTile * kHid / 4 / (64 * kGradRows);  // float4 of a tile per lane
+  static_assert(kTile <= 4 * 64 && kTile % 16 == 0, "a wavefront loads its row of A with one float4 per lane");
+  __shared__ __align__(16) float D[2][kTile * kHid];
+  __shared__ __align__(16) float A[2][kGradRows][kTile];
+  const int lane = (int)threadIdx.x & 63;
+  const int wave = (int)uniform(threadIdx.x >> 6);
   const float* ws = a.ws + (size_t)blockIdx.y * a.wstride;
   size_t off = (size_t)blockIdx.y * a.np;  // of this workgroup's layer
-  const int j1 = (a.d + 2) / 2, j2 = (kHid + 2) / 2;
-  int job = (int)blockIdx.x;
-  auto put = [&](size_t t, float gi) {
+  const int j1 = row_groups(a.d), j2 = row_groups(kHid);
+  int job = (int)blockIdx.x, din = a.d;
+  const float *at = a.Xt, *dz = ws + a.o_dz(0);
+  const bool last = job >= j1 + 2 * j2;
+  if (last) {
+    job = 0;
+    off += (size_t)a.d * kHid + kHid + 2 * (kHid * kHid + kHid);
+    dz = ws + a.o_h3();
+  } else if (job >= j1) {
+    const int l = 1 + (job - j1) / j2;
+    job = (job - j1) % j2;
+    din = kHid;
+    off += (size_t)a.d * kHid + kHid + (size_t)(l - 1) * (kHid * kHid + kHid);
+    at = ws + a.o_ht(l - 1);
+    dz = ws + a.o_dz(l);
+  }
+  const int k = kGradRows * job + wave;
+  const bool live = last ? wave < 2 : k <= din;
+  const float* row = last ? ws + a.o_d4() : k < din ? at + (size_t)k * a.ns : nullptr;  // null: all ones
+
+  f32x4 q[kQ], qa = {1.f, 1.f, 1.f, 1.f};
+  auto request = [&](int t0) {  // the pitch holds whole tiles
+    const f32x4* src = reinterpret_cast<const f32x4*>(dz + (size_t)t0 * kHid) + threadIdx.x;
+#pragma unroll
+    for (int t = 0; t < kQ; ++t) q[t] = src[64 * kGradRows * t];
+    if (row && lane < kTile / 4) qa = reinterpret_cast<const f32x4*>(row + t0)[lane];
+  };
+  auto place = [&](int buf) {
+    f32x4* dst = reinterpret_cast<f32x4*>(D[buf]) + threadIdx.x;
+#pragma unroll
+    for (int t = 0; t < kQ; ++t) dst[64 * kGradRows * t] = q[t];
+    if (lane < kTile / 4) reinterpret_cast<f32x4*>(A[buf][wave])[lane] = qa;
+  };
+  float acc = 0.f;
+  request(0);
+  place(0);
+  __syncthreads();
+  int buf = 0;
+  for (int t0 = 0; t0 < a.n; t0 += kTile, buf ^= 1) {
+    const bool more = t0 + kTile < a.n;
+    if (more) request(t0 + kTile);
+    const int cnt = min(kTile, a.n - t0);
+    const float* av = A[buf][wave];
+    const float* dv = D[buf] + lane;
+    if (last && wave == 1) {
+      for (int i = 0; i < cnt; ++i) acc += av[i];
+    } else {
+      int i = 0;
+#pragma unroll 2
+      for (; i + 16 <= cnt; i += 16) {
+#pragma unroll
+        for (int u = 0; u < 16; u += 4) {
+          const float4 x = *reinterpret_cast<const float4*>(av + i + u);
+          acc = __builtin_fmaf(x.x, dv[(i + u) * kHid], acc);
+          acc = __builtin_fmaf(x.y, dv[(i + u + 1) * kHid], acc);
+          acc = __builtin_fmaf(x.z, dv[(i + u + 2) * kHid], acc);
+          acc = __builtin_fmaf(x.w, dv[(i + u + 3) * kHid], acc);
+        }
+      }
+      for (; i < cnt; ++i) acc = __builtin_fmaf(av[i], dv[i * kHid], acc);
+    }
+    if (more) place(buf ^ 1);
+    __syncthreads();
+  }
+  auto put = [&](size_t t) {
     if constexpr (UPDATE) {
-      const float mi = ad.b1 * a.m[t] + (1.f - ad.b1) * gi;
-      const float vi = ad.b2 * a.v[t] + (1.f - ad.b2) * gi * gi;
+      const float mi = ad.b1 * a.m[t] + (1.f - ad.b1) * acc;
+      const float vi = ad.b2 * a.v[t] + (1.f - ad.b2) * acc * acc;
       a.m[t] = mi;
       a.v[t] = vi;
       a.p[t] = a.p[t] - ad.lr * (mi / ad.bc1) / (sqrtf(vi / ad.bc2) + ad.eps);
     } else {
-      a.g[t] = gi;
+      a.g[t] = acc;
     }
   };
-  float s0 = 0.f, s1 = 0.f;
-  if (job < j1 + 2 * j2) {
-    int din = a.d;
-    const float *at = a.Xt, *dz = ws + a.o_dz(0);
-    if (job >= j1) {
-      const int l = 1 + (job - j1) / j2;
-      job = (job - j1) % j2;
-      din = kHid;
-      off += (size_t)a.d * kHid + kHid + (size_t)(l - 1) * (kHid * kHid + kHid);
-      at = ws + a.o_ht(l - 1);
-      dz = ws + a.o_dz(l);
-    }
-    const int k0 = 2 * job, k1 = 2 * job + 1;
-    chains<kHid>(A, k0 < din ? at + (size_t)k0 * a.ns : nullptr, k1 < din ? at + (size_t)k1 * a.ns : nullptr, dz + lane,
-                 a.n, lane, s0, s1);
-    put(off + (size_t)k0 * kHid + lane, s0);
-    if (k1 <= din) put(off + (size_t)k1 * kHid + lane, s1);
+  if (!live) return;
+  if (last && wave == 1) {
+    if (lane == 0) put(off + kHid);
   } else {
-    off += (size_t)a.d * kHid + kHid + 2 * (kHid * kHid + kHid);
-    const float* d4 = ws + a.o_d4();
-    if (job == j1 + 2 * j2) {
-      chains<1>(A, d4, d4, ws + a.o_ht(2) + (size_t)lane * a.ns, a.n, lane, s0, s1);
-      put(off + lane, s0);
-    } else {
-      chains<1>(A, nullptr, nullptr, d4, a.n, lane, s0, s1);
-      if (lane == 0) put(off + kHid, s0);
-    }
+    put(off + (size_t)k * kHid + lane);
   }
 }
 
@@ -478,7 +499,7 @@ static AdamArgs adam_args(int t, float lr) {
 static int train_step(const MlpArgs& a, int cnt, int t, float lr, hipStream_t st) {
   int rc = rows<true>(a, cnt, st);
   if (rc != HF_OK) return rc;
-  HF_LAUNCH(k_grads<true>, dim3(grad_jobs(a.d), cnt), dim3(64), 0, st, a, adam_args(t, lr));
+  HF_LAUNCH(k_grads<true>, dim3(grad_jobs(a.d), cnt), dim3(64 * kGradRows), 0, st, a, adam_args(t, lr));
   return HF_OK;
 }
 
@@ -811,7 +832,7 @@ int hf_mlp_grad(const float* X, const float* y, int n, float* loss_out, float* g
   if ((rc = upload(M->X, X, (size_t)n * M->d, nullptr)) || (rc = upload(M->y, y, n, nullptr)) ||
       (rc = transpose(a, M, nullptr)) || (rc = rows<true>(a, 1, nullptr)))
     return rc;
-  HF_LAUNCH(k_grads<false>, dim3(grad_jobs(a.d), 1), dim3(64), 0, nullptr, a, AdamArgs{});
+  HF_LAUNCH(k_grads<false>, dim3(grad_jobs(a.d), 1), dim3(64 * kGradRows), 0, nullptr, a, AdamArgs{});
   if ((rc = losses(a, M, 1, nullptr)) != HF_OK) return rc;
   if ((rc = download(loss_out, M->loss, 1, nullptr)) != HF_OK) return rc;
   return download(grad_out, M->g, M->np, nullptr);

@@ -74,6 +74,64 @@ def test_gradient_matches_reference():
     assert o == g.size
 
 
+def _clear_of_the_kinks(p, n, d, seed):
+    """n samples none of whose hidden units lies so near zero that rounding
+    could flip its ReLU (for such a unit the gradient is not a function that
+    float32 can be compared on)."""
+    X = inputs.rng(seed).standard_normal((8 * n + 64, d)).astype(np.float32)
+    _, (_, pres) = ref.forward(p, X)
+    near = np.min([np.abs(z).min(axis=1) for z in pres[:-1]], axis=0)
+    X = np.ascontiguousarray(X[near > 1e-4][:n])
+    assert len(X) == n
+    return X, np.sin(X[:, 0]).astype(np.float32)
+
+
+@pytest.mark.parametrize("n,d", [(1, 1), (3, 2), (15, 3), (16, 4), (17, 5), (127, 42), (128, 63), (129, 64), (257, 65),
+                                 (300, 200)])
+def test_gradient_at_the_edges_of_tiles(n, d):
+    """Sample counts around a workgroup's 16 samples and a tile's 128, feature
+    counts around a workgroup's four rows: gradient, loss and prediction
+    against float64.  A float32 chain of k terms is off by at most k * 2^-24
+    of the sum of their magnitudes; four layers and the n samples bound every
+    gradient by (d + 192 + n) * 2^-23 of the gradient taken with magnitudes."""
+    H.hf_mlp_init(d, 21)
+    p = H.hf_mlp_get_params().astype(np.float64)
+    X, y = _clear_of_the_kinks(p, n, d, 100 + n)
+    loss, g = H.hf_mlp_grad(X, y)
+    rl, rg = ref.grad(p, X, y)
+    # the same sums with every factor's magnitude (no cancellation)
+    layers = ref.unpack(np.abs(p), d)
+    acts = [np.abs(X.astype(np.float64))]
+    for W, b in layers:
+        acts.append(acts[-1] @ W + b)
+    dz = (2.0 / n) * (acts[-1][:, 0] + np.abs(y))[:, None]
+    mags = []
+    for li in reversed(range(len(layers))):
+        mags.insert(0, np.concatenate([(acts[li].T @ dz).ravel(), dz.sum(axis=0)]))
+        dz = dz @ layers[li][0].T
+    eps = (d + 192 + n) * 2.0 ** -23
+    assert np.all(np.abs(g.astype(np.float64) - rg) <= eps * np.concatenate(mags))
+    big = (acts[-1][:, 0] + np.abs(y)) ** 2
+    assert abs(loss - rl) <= eps * big.mean()
+    want, _ = ref.forward(p, X)
+    assert np.all(np.abs(H.hf_mlp_predict(X) - want) <= eps * acts[-1][:, 0])
+
+
+def test_members_train_as_they_do_alone():
+    """Training side by side gives every member the bits it gets alone."""
+    X, y = _data(300, 31)
+    H.hf_mlp_init(D, 50, members=3)
+    H.hf_mlp_train(X, y, epochs=7, lr=1e-3)
+    both = H.hf_mlp_predict(X[:40]).astype(np.float64)
+    alone = []
+    for k in range(3):
+        H.hf_mlp_init(D, 50 + k)
+        H.hf_mlp_train(X, y, epochs=7, lr=1e-3)
+        alone.append(H.hf_mlp_predict(X[:40]).astype(np.float64))
+    # the mean of three float32 predictions, each rounded once more when alone
+    assert np.all(np.abs(both - np.mean(alone, axis=0)) <= 4 * 2.0 ** -24 * np.abs(alone).max(axis=0) + 2.0 ** -22)
+
+
 def test_adam_step_matches_reference():
     H.hf_mlp_init(D, 5)
     H.hf_mlp_adam_reset()
