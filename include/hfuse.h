@@ -140,7 +140,10 @@ typedef struct {
  *   block        workgroup size d0 in lanes: 256, 512 or 1024.
  *   vgpr_cap     per-lane VGPR bound of the compiled variant (0 = none); one of
  *                0, 64, 80, 96, 128 (Sec. III-B "Limit Register Usage").
- *   grid         workgroups per launch; 0 = occupancy-derived default.       */
+ *   grid         workgroups per launch, for both tasks; 0 = the default: each task
+ *                its own number of workgroups (the resident ones, or one for every
+ *                unit of work of a kernel that streams through memory), the launch
+ *                the larger of the two.                                      */
 typedef struct {
   int32_t split_waves;
   int32_t block;
@@ -230,7 +233,7 @@ typedef struct {
   int32_t wg_per_cu;      /* resident workgroups per CU at this block size           */
   int32_t waves_per_simd; /* resident wavefronts per SIMD                            */
   int32_t num_cus;        /* compute units of the device                             */
-  int32_t default_grid;   /* grid hf_run_* uses when grid == 0                       */
+  int32_t default_grid;   /* workgroups resident on the device at once               */
 } hf_kernel_info;
 /* Resources of the fused instantiation for (pair kinds, block, cap). */
 int hf_fused_info(int kind_a, int kind_b, int block, int vgpr_cap, hf_kernel_info* out);

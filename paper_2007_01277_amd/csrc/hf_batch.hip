@@ -386,7 +386,7 @@ static int batch_create(const hf_task* tasks, int ntask, const int32_t* group_of
     const int64_t nb = scratch_bytes(&tasks[i]);
     if (nb > 0 && !tasks[i].scratch) {
       soff[i] = sbytes;
-      sbytes += ((size_t)nb + 255) & ~size_t(255);
+      sbytes += (own_scratch_bytes(&tasks[i]) + 255) & ~size_t(255);
     }
   }
   hipError_t e;
@@ -410,7 +410,7 @@ static int batch_create(const hf_task* tasks, int ntask, const int32_t* group_of
   for (int i = 0; i < ntask; ++i) {
     void* scr = tasks[i].scratch ? tasks[i].scratch
                                  : (scratch_bytes(&tasks[i]) > 0 ? (char*)B->scratch + soff[i] : nullptr);
-    if ((rc = prepare(&tasks[i], scr, &dts[i])) != HF_OK) {
+    if ((rc = prepare(&tasks[i], scr, !tasks[i].scratch, &dts[i])) != HF_OK) {
       batch_free(B);
       return rc;
     }

@@ -42,12 +42,14 @@ struct MixArgs {  // R rounds of xorshift32 + multiply-add per uint32
 struct HistArgs {  // 256-bin histogram of bytes
   const uint8_t* in;
   uint32_t* out;
-  uint32_t* acc;  // [256] merged counts (zero between launches)
-  uint32_t* ctr;  // [1] workgroup arrival counter (zero between launches)
+  uint32_t* acc;  // [sums][256] merged counts (zero between launches)
+  uint32_t* ctr;  // workgroup arrival counter, then (sums > 1) one per accumulator,
+                  // a line apart (zero between launches)
   uint32_t n;
   uint32_t head;        // bytes before the first 16-byte aligned address
   uint32_t n16;         // aligned 16-byte vectors after the head
   uint32_t tail_start;  // head + 16 * n16
+  uint32_t sums;        // accumulators: LdsHist::kSums, or 1 in caller scratch
 };
 
 struct Im2colArgs {  // patches -> columns, [N][C*kh*kw][Ho*Wo]
@@ -78,7 +80,7 @@ struct UpArgs {  // bilinear upsampling by integer factor s, half-pixel centres
   FastDiv div_ho, div_row;  // div_row: by Wo4 (vector) or Wo
   uint32_t row2;            // the scale-2 row path (see Upsample)
   uint32_t nch;             // row path: chunks of 32 input columns per row, ceil(W / 32)
-  uint32_t nq;              // row path: units per plane, ceil(Ho * nch / 4)
+  uint32_t nq;              // row path: units per plane, ceil(bands * nch / 4)
   uint32_t row_units;       // row path: N * C * nq
   FastDiv div_nq, div_nch;
 };
@@ -460,13 +462,21 @@ struct IntMix {
 // instruction that see the same (frequent) value hit different words in
 // different banks instead of serialising on one address.  The interval's
 // barriers separate clearing, counting and merging.  Workgroups add their bins
-// into an agent-scope accumulator; the last workgroup to arrive moves the
-// totals to the output with atomic exchanges, which also re-zero it.
+// into one of `sums` agent-scope accumulators (workgroup w into number w % sums);
+// the last workgroup to arrive sums those that were used into the output and
+// re-zeroes them.  The additions of all dies to one accumulator line are done
+// one after the other, about 17 ns per workgroup, which was what bounded the
+// kernel while there was one accumulator (2^26 bytes alone: 46, 29 and 21 us at
+// 2048, 1024 and 512 workgroups); sixteen of them divide that serial part by
+// sixteen.  A caller's scratch holds one (hf_scratch_bytes is part of the
+// interface), the library's own has room for all.  A launch of one workgroup (small instances of a batch) has nothing to merge and writes its bins.
 #ifndef HF_HIST_COPIES
 #define HF_HIST_COPIES 16
 #endif
 struct LdsHist {
   static constexpr uint32_t kCopies = HF_HIST_COPIES;
+  static constexpr uint32_t kSums = 16;
+  static constexpr uint32_t kVecs = 2;
   static constexpr uint32_t lds_words(int) { return 256u * kCopies; }
 
   __device__ static __forceinline__ void count_byte(uint32_t* mine, uint32_t b) {
@@ -496,47 +506,79 @@ struct LdsHist {
     const uint32_t gl = p.wg * p.nlanes + p.lane;
     const uint32_t stride = p.nwg * p.nlanes;
     const uint4* v16 = reinterpret_cast<const uint4*>(a.in + a.head);
-    // Two vectors per step, and the next step's two requested before this
-    // step's atomics, so up to four 16-byte loads per lane are in flight:
-    // inside a fused kernel the interval may have only a few wavefronts per
-    // CU, and their loads alone must keep the input streaming.  The loop has
-    // no stores, so each wait covers only the loads it needs.
+    // kVecs vectors per step, and the next step's requested before this step's
+    // atomics, so up to 2 kVecs 16-byte loads per lane are in flight: inside a
+    // fused kernel the interval may have only a few wavefronts per CU, and
+    // their loads alone must keep the input streaming (four vectors: 19.5 us
+    // alone instead of 18.4 on 2^26 bytes, the fused pairs unchanged).  The loop
+    // has no stores, so each wait covers only the loads it needs.
     if (gl < a.n16) {
       const uint32_t last = a.n16 - 1u;
-      uint4 q0 = v16[gl], q1 = v16[min(gl + stride, last)];
+      uint4 q[kVecs], nx[kVecs];
+#pragma unroll
+      for (uint32_t k = 0; k < kVecs; ++k) q[k] = v16[min(gl + k * stride, last)];
       uint32_t i = gl;
-      for (; i + stride < a.n16; i += 2u * stride) {
-        const uint4 p0 = v16[min(i + 2u * stride, last)], p1 = v16[min(i + 3u * stride, last)];
-        count_vec(mine, q0);
-        count_vec(mine, q1);
-        q0 = p0;
-        q1 = p1;
+      for (; i + (kVecs - 1u) * stride < a.n16; i += kVecs * stride) {
+#pragma unroll
+        for (uint32_t k = 0; k < kVecs; ++k) nx[k] = v16[min(i + (kVecs + k) * stride, last)];
+#pragma unroll
+        for (uint32_t k = 0; k < kVecs; ++k) {
+          count_vec(mine, q[k]);
+          q[k] = nx[k];
+        }
       }
-      if (i < a.n16) count_vec(mine, q0);  // the last vector of an odd count
+#pragma unroll
+      for (uint32_t k = 0; k + 1u < kVecs; ++k)  // what a whole step does not cover
+        if (i + k * stride < a.n16) count_vec(mine, q[k]);
     }
     if (gl < a.head) count_byte(mine, a.in[gl]);
     for (uint32_t i = a.tail_start + gl; i < a.n; i += stride) count_byte(mine, a.in[i]);
     bar.sync();
 
+    const bool many = a.sums == kSums;
+    const uint32_t mine_sum = many ? p.wg % kSums : 0u;
+    uint32_t* acc = a.acc + 256u * mine_sum;
     for (uint32_t b = p.lane; b < 256u; b += p.nlanes) {
       uint32_t s = 0;
 #pragma unroll
       for (uint32_t k = 0; k < kCopies; ++k) s += lds[b * kCopies + k];
-      if (s) __hip_atomic_fetch_add(a.acc + b, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (p.nwg == 1u) a.out[b] = s;
+      else if (s) __hip_atomic_fetch_add(acc + b, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    if (p.nwg == 1u) return;
     wait_vmem();  // this wave's merge atomics have completed ...
     bar.sync();   // ... before wave 0 of the interval counts the workgroup in
 
-    if (p.wave == 0) {
-      uint32_t old = 0;
-      if (lane == 0) old = arrive_after_coherent_stores(a.ctr);
-      old = uniform(old);
-      if (old == p.nwg - 1u) {
-        for (uint32_t b = lane; b < 256u; b += 64u)
-          a.out[b] = __hip_atomic_exchange(a.acc + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (lane == 0) store_agent(a.ctr, 0u);
+    if (p.wave == 0 && lane == 0) {
+      uint32_t last = 0;
+      if (many && p.nwg > 4u * kSums) {
+        // the last of each accumulator's workgroups counts the accumulator in
+        uint32_t* sub = a.ctr + 32u * (1u + mine_sum);
+        const uint32_t of = (p.nwg - mine_sum + kSums - 1u) / kSums;
+        if (arrive_after_coherent_stores(sub) == of - 1u) {
+          store_agent(sub, 0u);
+          last = arrive_after_coherent_stores(a.ctr) == kSums - 1u;
+        }
+      } else {
+        last = arrive_after_coherent_stores(a.ctr) == p.nwg - 1u;
       }
+      lds[0] = last;
     }
+    bar.sync();
+    if (uniform(lds[0]) == 0u) return;
+    const uint32_t used = min(p.nwg, a.sums);
+    for (uint32_t b = p.lane; b < 256u; b += p.nlanes) {
+      uint32_t v[kSums], s = 0;  // every accumulator is requested before the first is used
+#pragma unroll
+      for (uint32_t k = 0; k < kSums; ++k) v[k] = load_agent(a.acc + 256u * min(k, used - 1u) + b);
+#pragma unroll
+      for (uint32_t k = 0; k < kSums; ++k) {
+        s += k < used ? v[k] : 0u;
+        if (k < used) store_agent(a.acc + 256u * k + b, 0u);
+      }
+      a.out[b] = s;
+    }
+    if (p.lane == 0) store_agent(a.ctr, 0u);
   }
 };
 
@@ -565,8 +607,11 @@ struct LdsHist {
 // outside the image load zero, which is exactly the zero padding, and lanes
 // past the plane's end store nothing, so the loop has no branch around a
 // memory access.  Each store instruction writes four chunks of one plane.
-// kStep units per step: their loads are issued together, so the wait for them
-// comes once per kStep units.
+// kStep units per step (fewer when a wavefront has fewer): their loads are
+// issued together, so the wait for them comes once per kStep units.  Wavefronts
+// take steps in turn, so that all of them work on one window of the tensors;
+// a contiguous range of units for each keeps 8192 places of DRAM open (with the
+// histogram of 2^26 bytes, inputs from HBM: 116 us in ranges, 109 in turn).
 struct Im2col {
   static constexpr uint32_t lds_words(int) { return 0; }
   static constexpr uint32_t kStep = 3;
@@ -574,9 +619,8 @@ struct Im2col {
   __device__ static void run_rows(const Im2colArgs& a, const Part& p, uint32_t lane) {
     const uint32_t nw = p.nwg * p.nwaves;
     const uint32_t gw = p.wg * p.nwaves + p.wave;
-    const uint32_t q = a.row_units / nw, r = a.row_units - q * nw;
-    const uint32_t ubeg = gw * q + min(gw, r);
-    const uint32_t uend = ubeg + q + (gw < r ? 1u : 0u);
+    const uint32_t per = (a.row_units + nw - 1u) / nw;  // units of the busiest wavefront
+    const uint32_t st = min(kStep, per);                // taken together
     const uint32_t W = a.W, H = a.H, HW = H * W, pbytes = 4u * HW;
     const uint32_t qrow = lane >> 4, c4 = lane & 15u;
     // The channel and output position of unit u in this lane (shared by both
@@ -587,13 +631,14 @@ struct Im2col {
       oh = fdiv(cid, a.div_nch);
       col = 64u * (cid - oh * a.nch) + 4u * c4;
     };
-    for (uint32_t u0 = ubeg; u0 < uend; u0 += kStep) {
+    for (uint32_t u0 = gw * st; u0 < a.row_units; u0 += nw * st) {
+      const uint32_t uend = min(u0 + st, a.row_units);
       float4 x[kStep][3];
       float edge[kStep][3];
 #pragma unroll
       for (uint32_t k = 0; k < kStep; ++k) {
         uint32_t nc, oh, col;
-        where(min(u0 + k, uend - 1u), nc, oh, col);  // a unit past the range repeats the last one
+        where(min(u0 + k, uend - 1u), nc, oh, col);  // a unit past the step repeats the last one
         const __amdgpu_buffer_rsrc_t src = buffer_rsrc(a.x + (size_t)nc * HW, pbytes);
         uint32_t ec = kOutOfRange;  // the column left or right of the lane's four, if another lane's
         if (c4 == 0u && col > 0u) ec = col - 1u;
@@ -694,77 +739,108 @@ struct Upsample {
   __device__ static __forceinline__ float lerp(float a, float b, float l) { return a + l * (b - a); }
 
   // Row path (scale 2, W even, 8-byte aligned input, 16-byte aligned output).
-  // Each output row is cut into chunks that read 32 input columns and write 64
-  // output columns; a unit is four consecutive chunks of one plane (four output
-  // rows when W <= 32), one chunk per 16-lane DPP row.  Lane 16q + c reads input
-  // columns 2c, 2c+1 of the output row's two source rows (one float2 each) and
-  // writes output columns 4c..4c+3 (one float4), so every store instruction
-  // covers whole contiguous lines.  Column 2c-1 comes from the lane before and
-  // column 2c+2 from the lane after by DPP row shifts, from one extra dword load
-  // at a chunk's first and last lane, and from the lane itself at the image's
-  // edges (the coordinate clamp).  The four outputs are the general scale-2
-  // path's expressions of the same inputs, so both paths give the same bits.
-  // Buffer accesses keep the loop free of branches around memory instructions;
-  // kStep units per step.
-  static constexpr uint32_t kStep = 4;
+  // A band of kBand input rows makes 2 kBand output rows and needs one input row
+  // more on either side, so a lane reads each row once and keeps its four
+  // horizontal interpolations for every output row that uses them.  Bands are
+  // cut into chunks that read 32 input columns and write 64 output columns; a
+  // unit is four consecutive chunks of one plane (four bands when W <= 32), one
+  // chunk per 16-lane DPP row.  Lane 16q + c reads input columns 2c, 2c+1 of its
+  // rows (one float2 each) and writes output columns 4c..4c+3 (one float4), so
+  // every store instruction covers whole contiguous lines.  Column 2c-1 comes
+  // from the lane before and column 2c+2 from the lane after by DPP row shifts,
+  // from one extra dword load at a chunk's first and last lane, and from the
+  // lane itself at the image's edges (the coordinate clamp).  The four outputs
+  // are the general scale-2 path's expressions of the same inputs, so both paths
+  // give the same bits.  Buffer accesses keep the loop free of branches around
+  // memory instructions.
+  //
+  // Bound by HBM (one byte read for four written).  [32,64,128,128] with its
+  // input in HBM, alone: 190 us with a unit per output row (every input row read
+  // by four units) and a contiguous range of units per wavefront; 175 us with
+  // the wavefronts taking units in turn, so that all of them work on one window
+  // of the tensors instead of keeping 8192 places of DRAM open; 140 us in bands
+  // of two input rows, 128 us in bands of four; 111 us with a workgroup for
+  // every unit (default_wgs), 6.0 TB/s.
+  static constexpr uint32_t kBand = 4;
+
+  struct Rows {
+    float2 x[kBand + 2];
+    float e[kBand + 2];
+  };
 
   __device__ static void run_rows(const UpArgs& a, const Part& p, uint32_t lane) {
     const uint32_t nw = p.nwg * p.nwaves;
-    const uint32_t gw = p.wg * p.nwaves + p.wave;
-    const uint32_t q = a.row_units / nw, r = a.row_units - q * nw;
-    const uint32_t ubeg = gw * q + min(gw, r);
-    const uint32_t uend = ubeg + q + (gw < r ? 1u : 0u);
     const uint32_t W = a.W, HW = a.H * a.W, OHW = a.Ho * a.Wo;
     const uint32_t qrow = lane >> 4, c4 = lane & 15u;
-    auto where = [&](uint32_t u, uint32_t& plane, uint32_t& oy, uint32_t& col) {
+    auto where = [&](uint32_t u, uint32_t& plane, uint32_t& y0, uint32_t& col) {
       plane = fdiv(u, a.div_nq);
       const uint32_t cid = 4u * (u - plane * a.nq) + qrow;  // chunk of this DPP row
-      oy = fdiv(cid, a.div_nch);
-      col = 32u * (cid - oy * a.nch) + 2u * c4;  // first input column of this lane
+      const uint32_t band = fdiv(cid, a.div_nch);
+      y0 = kBand * band;                                // first input row of the band
+      col = 32u * (cid - band * a.nch) + 2u * c4;       // first input column of this lane
     };
-    for (uint32_t u0 = ubeg; u0 < uend; u0 += kStep) {
-      float2 x0[kStep], x1[kStep];
-      float e0[kStep], e1[kStep];
+    auto load = [&](uint32_t u, Rows& r) {
+      uint32_t plane, y0, col;
+      where(u, plane, y0, col);
+      const bool ok = y0 < a.H && col < W;
+      const __amdgpu_buffer_rsrc_t src = buffer_rsrc(a.x + (size_t)plane * HW, 4u * HW);
+      uint32_t eo = kOutOfRange;  // the column left or right of the lane's two, if another lane's
+      if (c4 == 0u && col > 0u) eo = col - 1u;
+      if (c4 == 15u && col + 2u < W) eo = col + 2u;
 #pragma unroll
-      for (uint32_t k = 0; k < kStep; ++k) {
-        uint32_t plane, oy, col;
-        where(min(u0 + k, uend - 1u), plane, oy, col);  // a unit past the range repeats the last one
-        uint32_t y0, y1;
-        float ly;
-        coord(min(oy, a.Ho - 1u), a.inv_s, a.H, y0, y1, ly);
-        const bool ok = oy < a.Ho && col < W;
-        const __amdgpu_buffer_rsrc_t src = buffer_rsrc(a.x + (size_t)plane * HW, 4u * HW);
-        uint32_t eo = kOutOfRange;  // the column left or right of the lane's two, if another lane's
-        if (c4 == 0u && col > 0u) eo = col - 1u;
-        if (c4 == 15u && col + 2u < W) eo = col + 2u;
-        x0[k] = buffer_load2(src, ok ? 4u * (y0 * W + col) : kOutOfRange);
-        x1[k] = buffer_load2(src, ok ? 4u * (y1 * W + col) : kOutOfRange);
-        e0[k] = buffer_load1(src, ok && eo != kOutOfRange ? 4u * (y0 * W + eo) : kOutOfRange);
-        e1[k] = buffer_load1(src, ok && eo != kOutOfRange ? 4u * (y1 * W + eo) : kOutOfRange);
+      for (uint32_t i = 0; i < kBand + 2u; ++i) {
+        const uint32_t y = i == 0u ? (y0 > 0u ? y0 - 1u : 0u) : min(y0 + i - 1u, a.H - 1u);
+        r.x[i] = buffer_load2(src, ok ? 4u * (y * W + col) : kOutOfRange);
+        r.e[i] = buffer_load1(src, ok && eo != kOutOfRange ? 4u * (y * W + eo) : kOutOfRange);
       }
+    };
+    auto store = [&](uint32_t u, const Rows& r) {
+      uint32_t plane, y0, col;
+      where(u, plane, y0, col);
+      const bool first = col == 0u, last = col + 2u >= W, top = y0 == 0u;
+      const __amdgpu_buffer_rsrc_t dst = buffer_rsrc(a.out + (size_t)plane * OHW, 4u * OHW);
+      float h[kBand + 2][4];
 #pragma unroll
-      for (uint32_t k = 0; k < kStep; ++k) {
-        uint32_t plane, oy, col;
-        where(min(u0 + k, uend - 1u), plane, oy, col);
-        uint32_t y0, y1;
-        float ly;
-        coord(min(oy, a.Ho - 1u), a.inv_s, a.H, y0, y1, ly);
+      for (uint32_t i = 0; i < kBand + 2u; ++i) {
         // every lane takes part in the shifts (row_shr:1 / row_shl:1)
-        const float l0 = dpp_f32<0x111>(x0[k].y), r0 = dpp_f32<0x101>(x0[k].x);
-        const float l1 = dpp_f32<0x111>(x1[k].y), r1 = dpp_f32<0x101>(x1[k].x);
-        const bool first = col == 0u, last = col + 2u >= W;
-        const float p0 = first ? x0[k].x : (c4 == 0u ? e0[k] : l0), p1 = x0[k].x, p2 = x0[k].y;
-        const float p3 = last ? x0[k].y : (c4 == 15u ? e0[k] : r0);
-        const float q0 = first ? x1[k].x : (c4 == 0u ? e1[k] : l1), q1 = x1[k].x, q2 = x1[k].y;
-        const float q3 = last ? x1[k].y : (c4 == 15u ? e1[k] : r1);
-        const uint32_t at = (oy < a.Ho && col < W && u0 + k < uend) ? 4u * (oy * a.Wo + 2u * col) : kOutOfRange;
-        buffer_store4_nt(buffer_rsrc(a.out + (size_t)plane * OHW, 4u * OHW), at,
-                         lerp(lerp(p0, p1, 0.75f), lerp(q0, q1, 0.75f), ly),
-                         lerp(lerp(p1, p2, 0.25f), lerp(q1, q2, 0.25f), ly),
-                         lerp(lerp(p1, p2, 0.75f), lerp(q1, q2, 0.75f), ly),
-                         lerp(lerp(p2, p3, 0.25f), lerp(q2, q3, 0.25f), ly));
+        const float sl = dpp_f32<0x111>(r.x[i].y), sr = dpp_f32<0x101>(r.x[i].x);
+        const float p0 = first ? r.x[i].x : (c4 == 0u ? r.e[i] : sl), p1 = r.x[i].x, p2 = r.x[i].y;
+        const float p3 = last ? r.x[i].y : (c4 == 15u ? r.e[i] : sr);
+        h[i][0] = lerp(p0, p1, 0.75f);
+        h[i][1] = lerp(p1, p2, 0.25f);
+        h[i][2] = lerp(p1, p2, 0.75f);
+        h[i][3] = lerp(p2, p3, 0.25f);
       }
+#pragma unroll
+      for (uint32_t o = 0; o < 2u * kBand; ++o) {
+        // output row 2y lies between input rows y-1 and y (the image's first row
+        // is input row 0 with weight 0 on row 1), output row 2y+1 between y and y+1
+        const uint32_t i = o / 2u + (o & 1u);
+        float v[4];
+#pragma unroll
+        for (uint32_t c = 0; c < 4u; ++c) {
+          if (o == 0u)
+            v[c] = lerp(top ? h[1][c] : h[0][c], top ? h[2][c] : h[1][c], top ? 0.f : 0.75f);
+          else
+            v[c] = lerp(h[i][c], h[i + 1u][c], (o & 1u) ? 0.25f : 0.75f);
+        }
+        const uint32_t oy = 2u * y0 + o;
+        buffer_store4_nt(dst, oy < a.Ho && col < W ? 4u * (oy * a.Wo + 2u * col) : kOutOfRange, v[0], v[1], v[2], v[3]);
+      }
+    };
+    // the next unit is requested before this one is stored: the vector-memory
+    // counter retires in order, so the wait for loads issued after the stores
+    // would be a wait for the stores as well
+    uint32_t u = p.wg * p.nwaves + p.wave;
+    if (u >= a.row_units) return;
+    Rows cur, nxt;
+    load(u, cur);
+    for (; u + nw < a.row_units; u += nw) {
+      load(u + nw, nxt);
+      store(u, cur);
+      cur = nxt;
     }
+    store(u, cur);
   }
 
   __device__ static __forceinline__ float sample(const float* r0, const float* r1, float ly, uint32_t W,
@@ -852,7 +928,9 @@ struct Upsample {
 // the general path).  Rows clamp the same way.  Each window is scanned in the
 // general path's order, and values and indices are stored as float4 / int4
 // through buffer resources (lanes past the plane's end store nothing), four
-// chunks per store instruction.
+// chunks per store instruction.  Wavefronts take units in turn, as in upsample
+// ([64,64,112,112] with its input in HBM, alone: 63 us in contiguous ranges, 60
+// in turn, 56 with a workgroup for every unit).
 struct Maxpool {
   static constexpr int kSoloWaves = 8;  // 45 VGPRs, but 106 SGPRs would allow only 7
   static constexpr uint32_t kPer = 2;
@@ -869,12 +947,9 @@ struct Maxpool {
   __device__ static void run_rows(const PoolArgs& a, const Part& p, uint32_t lane) {
     const uint32_t nw = p.nwg * p.nwaves;
     const uint32_t gw = p.wg * p.nwaves + p.wave;
-    const uint32_t q = a.row_units / nw, r = a.row_units - q * nw;
-    const uint32_t ubeg = gw * q + min(gw, r);
-    const uint32_t uend = ubeg + q + (gw < r ? 1u : 0u);
     const uint32_t W = a.W, HW = a.H * a.W, OHW = a.Ho * a.Wo;
     const uint32_t qrow = lane >> 4, c4 = lane & 15u;
-    for (uint32_t u = ubeg; u < uend; ++u) {
+    for (uint32_t u = gw; u < a.row_units; u += nw) {
       const uint32_t plane = fdiv(u, a.div_nq);
       const uint32_t cid = 4u * (u - plane * a.nq) + qrow;  // chunk of this DPP row
       const uint32_t oh = fdiv(cid, a.div_nch);

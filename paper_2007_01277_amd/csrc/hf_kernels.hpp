@@ -8,6 +8,8 @@
 //               wavefronts [w1, BLOCK/64) run K2 with tid_2 = threadIdx.x - 64*w1,
 //               size_2 = BLOCK - 64*w1.  The test is on a wave-uniform value, so it
 //               compiles to a scalar branch, never to divergent lanes;
+//   grids     : body i runs in the first g_i workgroups, its own grid; in the
+//               others its wavefronts end at once and leave their slots;
 //   barriers  : each body gets its own interval barrier (PartBarrier).
 // WPE > 0 asks the compiler for at least WPE resident wavefronts per SIMD, which
 // bounds the VGPRs per lane to 512/WPE: the register bound of Sec. III-B.
@@ -32,7 +34,8 @@ template <> struct BodyOf<8> { using T = EthashLike; };
 constexpr uint32_t max1(uint32_t v) { return v ? v : 1u; }
 
 template <class K1, class K2, int BLOCK>
-__device__ __forceinline__ void fused_body(const DevTask& ta, const DevTask& tb, uint32_t w1) {
+__device__ __forceinline__ void fused_body(const DevTask& ta, const DevTask& tb, uint32_t w1, uint32_t g1,
+                                           uint32_t g2) {
   constexpr uint32_t L1 = K1::lds_words(BLOCK);
   constexpr uint32_t L2 = K2::lds_words(BLOCK);
   __shared__ uint32_t smem[2 + max1(L1 + L2)];
@@ -44,26 +47,29 @@ __device__ __forceinline__ void fused_body(const DevTask& ta, const DevTask& tb,
   const uint32_t wave = uniform(threadIdx.x >> 6);
   constexpr uint32_t W = BLOCK / 64;
   if (wave < w1) {
-    const Part p{threadIdx.x, 64u * w1, wave, w1, blockIdx.x, gridDim.x};
+    if (blockIdx.x >= g1) return;
+    const Part p{threadIdx.x, 64u * w1, wave, w1, blockIdx.x, g1};
     PartBarrier bar(&smem[0], w1);
     K1::run(ta, p, bar, &smem[2]);
   } else {
+    if (blockIdx.x >= g2) return;
     const uint32_t w2 = W - w1;
-    const Part p{threadIdx.x - 64u * w1, 64u * w2, wave - w1, w2, blockIdx.x, gridDim.x};
+    const Part p{threadIdx.x - 64u * w1, 64u * w2, wave - w1, w2, blockIdx.x, g2};
     PartBarrier bar(&smem[1], w2);
     K2::run(tb, p, bar, &smem[2 + L1]);
   }
 }
 
 template <class K1, class K2, int BLOCK>
-__global__ void __launch_bounds__(BLOCK) fused_nocap(DevTask ta, DevTask tb, uint32_t w1) {
-  fused_body<K1, K2, BLOCK>(ta, tb, w1);
+__global__ void __launch_bounds__(BLOCK) fused_nocap(DevTask ta, DevTask tb, uint32_t w1, uint32_t g1,
+                                                     uint32_t g2) {
+  fused_body<K1, K2, BLOCK>(ta, tb, w1, g1, g2);
 }
 
 template <class K1, class K2, int BLOCK, int WPE>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE)))
-fused_cap(DevTask ta, DevTask tb, uint32_t w1) {
-  fused_body<K1, K2, BLOCK>(ta, tb, w1);
+fused_cap(DevTask ta, DevTask tb, uint32_t w1, uint32_t g1, uint32_t g2) {
+  fused_body<K1, K2, BLOCK>(ta, tb, w1, g1, g2);
 }
 
 // Vertical fusion, the comparator of the paper (Sec. II-B "Vertical Kernel

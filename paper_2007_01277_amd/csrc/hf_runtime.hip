@@ -276,8 +276,16 @@ int64_t scratch_bytes(const hf_task* t) {
   }
 }
 
+// Scratch of a task in the library's own memory: a histogram there gets all
+// its accumulators.
+size_t own_scratch_bytes(const hf_task* t) {
+  if (t->kind == HF_LDS_HIST) return 4 * (256 * (size_t)LdsHist::kSums + 32 * (1 + (size_t)LdsHist::kSums));
+  return (size_t)std::max<int64_t>(scratch_bytes(t), 0);
+}
+
 // ------------------------------------------------------------------ marshalling
-int prepare(const hf_task* t, void* scratch, DevTask* dt) {
+// own: `scratch` has own_scratch_bytes(t), not just scratch_bytes(t).
+int prepare(const hf_task* t, void* scratch, bool own, DevTask* dt) {
   std::memset(dt, 0, sizeof(*dt));
   switch (t->kind) {
     case HF_BN_STATS: {
@@ -313,7 +321,8 @@ int prepare(const hf_task* t, void* scratch, DevTask* dt) {
       a.in = static_cast<const uint8_t*>(t->in);
       a.out = static_cast<uint32_t*>(t->out0);
       a.acc = static_cast<uint32_t*>(scratch);
-      a.ctr = static_cast<uint32_t*>(scratch) + 256;
+      a.sums = own ? LdsHist::kSums : 1u;
+      a.ctr = static_cast<uint32_t*>(scratch) + 256u * a.sums;
       a.n = (uint32_t)t->n;
       const uint32_t mis = (uint32_t)(reinterpret_cast<uintptr_t>(t->in) % 16u);
       a.head = std::min<uint32_t>(a.n, (16u - mis) % 16u);
@@ -375,7 +384,7 @@ int prepare(const hf_task* t, void* scratch, DevTask* dt) {
       a.row2 = s == 2u && a.W % 2u == 0u && (uint64_t)a.Ho * a.Wo * 4u < (1ull << 31) && aligned(t->in, 8) &&
                aligned(t->out0, 16);
       a.nch = (a.W + 31u) / 32u;
-      a.nq = (uint32_t)(((uint64_t)a.Ho * a.nch + 3u) / 4u);
+      a.nq = (uint32_t)(((uint64_t)((a.H + Upsample::kBand - 1u) / Upsample::kBand) * a.nch + 3u) / 4u);
       a.row_units = (uint32_t)t->n * (uint32_t)t->c * a.nq;
       a.div_nq = make_fastdiv(a.nq);
       a.div_nch = make_fastdiv(a.nch);
@@ -451,6 +460,23 @@ int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves) {
   return std::max<int64_t>(units, 1);
 }
 
+// Workgroups a task runs on by default, `waves` wavefronts of each, where
+// `resident` workgroups fit the chip at once.  Upsample and maxpool stream
+// through HBM and get a workgroup for every unit of work, however many that is:
+// workgroups start in order, so those in flight always work on one narrow window
+// of the tensors, where resident wavefronts that stride through them drift apart
+// (inputs from HBM, upsample x2 [32,64,128,128]: 128 us resident, 111 in order;
+// maxpool [64,64,112,112]: 60 and 56).  im2col, nine tenths of whose traffic is
+// writes, is no faster that way (97 us resident, 102 in order with its three
+// units per wavefront, 118 with one).  The other kinds keep state per workgroup
+// or per range of work (histogram bins and their merge, channel partials,
+// hoisted hash rounds).
+uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int resident) {
+  const int64_t need = useful_wgs(t, d, waves);
+  const bool stream = t->kind == HF_UPSAMPLE || t->kind == HF_MAXPOOL;
+  return (uint32_t)(stream ? std::min<int64_t>(need, INT32_MAX) : std::min<int64_t>(need, resident));
+}
+
 int occupancy_grid(DeviceState* s, const void* fn, int block, int* wg_per_cu) {
   int occ = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, block, 0);
@@ -471,7 +497,7 @@ int task_scratch(DeviceState* s, const hf_task* t, int slot, void** out) {
     *out = t->scratch;
     return HF_OK;
   }
-  return arena_slot(s, slot, (size_t)need, out);
+  return arena_slot(s, slot, own_scratch_bytes(t), out);
 }
 
 // ------------------------------------------------------------------ timing
@@ -517,11 +543,11 @@ int launch_solo(DeviceState* s, const hf_task* t, int block, int grid, int slot,
   int rc = task_scratch(s, t, slot, &scr);
   if (rc != HF_OK) return rc;
   DevTask d;
-  if ((rc = prepare(t, scr, &d)) != HF_OK) return rc;
+  if ((rc = prepare(t, scr, !t->scratch, &d)) != HF_OK) return rc;
   if (grid <= 0) {
     const int g = occupancy_grid(s, k->fn, block, nullptr);
     if (g < 0) return g;
-    grid = (int)std::min<int64_t>(g, useful_wgs(t, d, block / 64));
+    grid = (int)default_wgs(t, d, block / 64, g);
   }
   void* args[] = {&d};
   hipError_t e = hipLaunchKernel(k->fn, dim3(grid), dim3(block), args, 0, st);
@@ -545,8 +571,8 @@ int validate_fused(const hf_pair* pr, const hf_config* cfg) {
   return HF_OK;
 }
 
-int launch_fused(DeviceState* s, const hf_pair* pr, const hf_config* cfg, hipStream_t st,
-                 int* grid_used) {
+int launch_fused(DeviceState* s, const hf_pair* pr, const hf_config* cfg, hipStream_t st, int* grid_used,
+                 int own_mask) {
   int rc = validate_fused(pr, cfg);
   if (rc != HF_OK) return rc;
   // instantiations exist for kind_a <= kind_b; the mirrored pair swaps the intervals
@@ -564,17 +590,19 @@ int launch_fused(DeviceState* s, const hf_pair* pr, const hf_config* cfg, hipStr
   if ((rc = task_scratch(s, ta, 0, &sa)) != HF_OK) return rc;
   if ((rc = task_scratch(s, tb, 1, &sb)) != HF_OK) return rc;
   DevTask da, db;
-  if ((rc = prepare(ta, sa, &da)) != HF_OK || (rc = prepare(tb, sb, &db)) != HF_OK) return rc;
-  int grid = cfg->grid;
-  if (grid <= 0) {
+  const bool own_a = !ta->scratch || (own_mask & (ta == &pr->a ? 1 : 2));
+  const bool own_b = !tb->scratch || (own_mask & (tb == &pr->a ? 1 : 2));
+  if ((rc = prepare(ta, sa, own_a, &da)) != HF_OK || (rc = prepare(tb, sb, own_b, &db)) != HF_OK) return rc;
+  uint32_t uw1 = (uint32_t)w1, g1 = (uint32_t)cfg->grid, g2 = g1;
+  if (cfg->grid <= 0) {
     const int g = occupancy_grid(s, k->fn, cfg->block, nullptr);
     if (g < 0) return g;
-    const int64_t need = std::max(useful_wgs(ta, da, w1), useful_wgs(tb, db, W - w1));
-    grid = (int)std::min<int64_t>(g, need);
+    g1 = default_wgs(ta, da, w1, g);
+    g2 = default_wgs(tb, db, W - w1, g);
   }
+  const int grid = (int)std::max(g1, g2);
   if (grid_used) *grid_used = grid;
-  uint32_t uw1 = (uint32_t)w1;
-  void* args[] = {&da, &db, &uw1};
+  void* args[] = {&da, &db, &uw1, &g1, &g2};
   hipError_t e = hipLaunchKernel(k->fn, dim3(grid), dim3(cfg->block), args, 0, st);
   return e == hipSuccess ? HF_OK : record_hip(e);
 }
@@ -827,16 +855,23 @@ int hf_run_fused_noalloc(const hf_pair* pr, const hf_config* cfg, void* stream) 
   hf_pair p = *pr;
   hf_task* ts[2] = {&p.a, &p.b};
   size_t off[2] = {0, 0}, total = 0;
-  bool mine[2] = {false, false};
-  for (int i = 0; i < 2; ++i) {
-    const int64_t need = scratch_bytes(ts[i]);
-    if (need > 0 && !ts[i]->scratch) {
-      mine[i] = true;
-      off[i] = total;
-      total += ((size_t)need + 255) & ~size_t(255);
+  bool mine[2] = {false, false}, own = true;
+  auto place = [&] {
+    total = 0;
+    for (int i = 0; i < 2; ++i) {
+      const int64_t need = scratch_bytes(ts[i]);
+      if (need > 0 && !ts[i]->scratch) {
+        mine[i] = true;
+        off[i] = total;
+        total += ((own ? own_scratch_bytes(ts[i]) : (size_t)need) + 255) & ~size_t(255);
+      }
     }
+    return total <= (size_t)HF_NOALLOC_SCRATCH_BYTES;
+  };
+  if (!place()) {  // regions of hf_scratch_bytes, as a caller would give them
+    own = false;
+    if (!place()) return HF_ESCRATCH;
   }
-  if (total > (size_t)HF_NOALLOC_SCRATCH_BYTES) return HF_ESCRATCH;
   DeviceState* s = device_state(&rc);
   if (!s) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -852,7 +887,7 @@ int hf_run_fused_noalloc(const hf_pair* pr, const hf_config* cfg, void* stream) 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return record_hip(e);
   }
-  return launch_fused(s, &p, cfg, st, nullptr);
+  return launch_fused(s, &p, cfg, st, nullptr, own ? (mine[0] ? 1 : 0) | (mine[1] ? 2 : 0) : 0);
 }
 
 int hf_run_fused(const hf_pair* pr, int split_num, int split_den, int block, int vgpr_cap,
@@ -883,7 +918,7 @@ int hf_run_vfused(const hf_pair* pr, int block, int grid, void* stream, float* m
   void *sa = nullptr, *sb = nullptr;
   if ((rc = task_scratch(s, ta, 0, &sa)) != HF_OK || (rc = task_scratch(s, tb, 1, &sb)) != HF_OK) return rc;
   DevTask da, db;
-  if ((rc = prepare(ta, sa, &da)) != HF_OK || (rc = prepare(tb, sb, &db)) != HF_OK) return rc;
+  if ((rc = prepare(ta, sa, !ta->scratch, &da)) != HF_OK || (rc = prepare(tb, sb, !tb->scratch, &db)) != HF_OK) return rc;
   if (grid <= 0) {
     const int g = occupancy_grid(s, k->fn, block, nullptr);
     if (g < 0) return g;

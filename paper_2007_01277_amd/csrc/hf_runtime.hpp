@@ -41,10 +41,13 @@ int check_block(int block);
 int validate_task(const hf_task* t);
 int validate_fused(const hf_pair* pr, const hf_config* cfg);
 int64_t scratch_bytes(const hf_task* t);
-int prepare(const hf_task* t, void* scratch, DevTask* dt);
+size_t own_scratch_bytes(const hf_task* t);
+int prepare(const hf_task* t, void* scratch, bool own, DevTask* dt);
 int arena_slot(DeviceState* s, int i, size_t bytes, void** out);
 int launch_solo(DeviceState* s, const hf_task* t, int block, int grid, int slot, hipStream_t st);
-int launch_fused(DeviceState* s, const hf_pair* pr, const hf_config* cfg, hipStream_t st, int* grid_used);
+// own_mask: bit 0 (1): the scratch set in pr->a (pr->b) is a region of own_scratch_bytes
+int launch_fused(DeviceState* s, const hf_pair* pr, const hf_config* cfg, hipStream_t st, int* grid_used,
+                 int own_mask = 0);
 int launch_unfused(DeviceState* s, const hf_pair* pr, int block_a, int block_b, int mode,
                    hipStream_t s0, hipStream_t s1);
 int wait_event(hipEvent_t ev);

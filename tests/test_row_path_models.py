@@ -217,3 +217,70 @@ def test_maxpool_row_model_equals_the_oracle(shape, mode):
     rv, ri = oracle.maxpool(x, 3, 3, 2, 1)
     assert np.array_equal(v, rv, equal_nan=True)
     assert np.array_equal(i, ri)
+
+
+def upsample2_bands(x, band=4):
+    """The scale-2 row path's present decomposition: a chunk covers `band` input
+    rows and makes 2*band output rows; each lane interpolates its band + 2 input
+    rows horizontally once and combines neighbours vertically."""
+    N, C, H, W = x.shape
+    Ho, Wo = 2 * H, 2 * W
+    HW, OHW = H * W, Ho * Wo
+    xf = x.reshape(N * C, HW)
+    out = np.full((N * C, OHW), 7.0, np.float32)
+    nch = (W + 31) // 32
+    nq = ((H + band - 1) // band * nch + 3) // 4
+    for u in range(N * C * nq):
+        pl = u // nq
+        for q in range(4):
+            cid = 4 * (u - pl * nq) + q
+            b = cid // nch
+            y0 = band * b
+            lanes = []
+            for c4 in range(16):
+                col = 32 * (cid - b * nch) + 2 * c4
+                ok = y0 < H and col < W
+                ec = col - 1 if c4 == 0 and col > 0 else (col + 2 if c4 == 15 and col + 2 < W else OOR)
+                rows = []
+                for i in range(band + 2):
+                    y = max(y0 - 1, 0) if i == 0 else min(y0 + i - 1, H - 1)
+                    v = _load(xf[pl], 4 * (y * W + col) if ok else OOR, 2, 4 * HW)
+                    e = _load(xf[pl], 4 * (y * W + ec) if ok and ec != OOR else OOR, 1, 4 * HW)[0]
+                    rows.append((v, e))
+                lanes.append(rows)
+            for c4 in range(16):
+                col = 32 * (cid - b * nch) + 2 * c4
+                h = []
+                for i in range(band + 2):
+                    v, e = lanes[c4][i]
+                    sl = lanes[c4 - 1][i][0][1] if c4 > 0 else np.float32(0)
+                    sr = lanes[c4 + 1][i][0][0] if c4 < 15 else np.float32(0)
+                    p0 = v[0] if col == 0 else (e if c4 == 0 else sl)
+                    p3 = v[1] if col + 2 >= W else (e if c4 == 15 else sr)
+                    h.append([_lerp(p0, v[0], .75), _lerp(v[0], v[1], .25), _lerp(v[0], v[1], .75),
+                              _lerp(v[1], p3, .25)])
+                for o in range(2 * band):
+                    oy = 2 * y0 + o
+                    if oy >= Ho or col >= W:
+                        continue
+                    i = o // 2 + (o & 1)
+                    top, bot, l = h[i], h[i + 1], .25 if o & 1 else .75
+                    if o == 0 and y0 == 0:
+                        top, bot, l = h[1], h[2], 0.0
+                    at = oy * Wo + 2 * col
+                    assert 4 * (at + 4) <= 4 * OHW
+                    out[pl, at:at + 4] = [_lerp(top[e], bot[e], l) for e in range(4)]
+    return out.reshape(N, C, Ho, Wo)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1, 2), (1, 2, 3, 64), (1, 1, 2, 34), (2, 1, 4, 128), (1, 1, 5, 200),
+                                   (1, 1, 9, 56), (1, 2, 17, 6)])
+@pytest.mark.parametrize("special", [False, True])
+def test_upsample2_band_model_gives_the_row_model_s_bits(shape, special):
+    g = np.random.default_rng(5)
+    x = g.standard_normal(shape).astype(np.float32)
+    if special:
+        x[g.random(shape) < 0.05] = np.inf
+        x[g.random(shape) < 0.05] = np.nan
+    with np.errstate(invalid="ignore"):
+        assert np.array_equal(upsample2_bands(x), upsample2_rows(x), equal_nan=True)
