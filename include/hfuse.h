@@ -449,7 +449,7 @@ int hf_selftest_barrier(int block, int split_waves, int iters_a, int iters_b, ui
                         void* stream, uint32_t* mismatches);
 /* Measured integer-issue ceiling of the int_mix round: `grid` workgroups of 256
  * lanes (0: eight per CU, the resident maximum) each run `rounds` rounds of
- * the round on four independent chains per lane from registers only (the
+ * the round on sixteen independent chains per lane from registers only (the
  * int_mix body's instruction mix without its loads and stores).  Writes the
  * lane-ops executed (8 per lane-round: 3 shifts, 3 xors, 1 multiply, 1 add)
  * to lane_ops_out (may be NULL). */

@@ -300,7 +300,7 @@ struct BnStats {
   // the end of each segment it arrives on the channel's counter, and the last
   // arriver merges the channel.
   template <bool VEC>
-  __device__ static void run_range(const BnArgs& a, uint32_t ubeg, uint32_t uend, uint32_t lane) {
+  __device__ static __forceinline__ void run_range(const BnArgs& a, uint32_t ubeg, uint32_t uend, uint32_t lane) {
     uint32_t c = fdiv(ubeg, a.div_upc);
     uint32_t k0 = ubeg - c * a.upc;
     for (uint32_t u = ubeg; u < uend; ++c, k0 = 0) {
@@ -315,7 +315,7 @@ struct BnStats {
   }
 
   template <class Bar>
-  __device__ static void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
+  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const BnArgs& a = dt.bn;
     const uint32_t lane = lane_id();
     const uint32_t nw = p.nwg * p.nwaves;
@@ -342,7 +342,7 @@ struct BnStats {
 
   // Merge the units of channel c: each lane merges units lane, lane+64, ... in
   // order, then the 64 lane results are merged by a fixed butterfly.
-  __device__ static void finish_channel(const BnArgs& a, uint32_t c, uint32_t lane) {
+  __device__ static __forceinline__ void finish_channel(const BnArgs& a, uint32_t c, uint32_t lane) {
     const uint32_t base = 2u * c * a.upc;
     double n = 0.0, m = 0.0, m2 = 0.0;
     for (uint32_t k = lane; k < a.upc; k += 64u) {
@@ -399,6 +399,18 @@ struct BnStats {
 // exposes one load and one store latency, and four vectors per step divide the
 // number of steps, and of exposed latencies, by four without computing any
 // vector twice.
+//
+// Bound by VALU issue.  On gfx950 some instructions issue at twice the rate of
+// the others (measured over independent chains, 8 waves per SIMD: and, or, xor,
+// 32-bit add, right shift, v_bitop3 and fp32 fma about 2.5 cycles at the nominal
+// 2.4 GHz; left shift, 32-bit multiply, v_alignbit and the three-operand adds
+// about 4.4; any of them with a scalar register operand 4.4), but only in
+// runs: alternating one fast and one slow instruction runs at the slow rate
+// throughout.  So a round goes over all words of a step one operation at a time,
+// in an order the compiler may not undo, and takes the slow operations three
+// instead of four: the multiply and the addition are one 64-bit multiply-add
+// whose high half is not used.  2^24 words of 128 rounds: 424 us word by word,
+// 378 in runs of the same operation, 366 with the multiply-add.
 struct IntMix {
   static constexpr uint32_t lds_words(int) { return 0; }
 
@@ -409,28 +421,59 @@ struct IntMix {
     return x * 2654435761u + r;
   }
 
+  // R rounds on N words, one operation at a time over all of them.
+  template <uint32_t N>
+  __device__ static __forceinline__ void rounds(uint32_t (&x)[N], uint32_t R) {
+    uint32_t t[N], mul = 2654435761u;
+    asm("" : "+v"(mul));  // in a vector register: the round index is the one scalar operand
+#pragma unroll
+    for (uint32_t k = 0; k < N; ++k) t[k] = x[k] << 13;
+    for (uint32_t r = 0; r < R; ++r) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (uint32_t k = 0; k < N; ++k) x[k] ^= t[k];
+#pragma unroll
+      for (uint32_t k = 0; k < N; ++k) x[k] ^= x[k] >> 17;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (uint32_t k = 0; k < N; ++k) t[k] = x[k] << 5;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (uint32_t k = 0; k < N; ++k) x[k] ^= t[k];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (uint32_t k = 0; k < N; ++k) {
+        uint64_t d = (uint64_t)x[k] * mul + r;
+        asm("" : "+v"(d));  // both halves: one multiply-add instead of a multiply and an add
+        x[k] = (uint32_t)d;
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < N; ++k) t[k] = x[k] << 13;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
   // vectors i, i + stride, ..., i + (K-1)*stride, all in range
   template <uint32_t K>
   __device__ static __forceinline__ void step(const uint4* in4, uint4* out4, uint32_t i, uint32_t stride,
                                               uint32_t R) {
-    uint4 v[K];
+    uint32_t x[4 * K];
 #pragma unroll
-    for (uint32_t k = 0; k < K; ++k) v[k] = in4[i + k * stride];
-    for (uint32_t r = 0; r < R; ++r) {
-#pragma unroll
-      for (uint32_t k = 0; k < K; ++k) {
-        v[k].x = round1(v[k].x, r);
-        v[k].y = round1(v[k].y, r);
-        v[k].z = round1(v[k].z, r);
-        v[k].w = round1(v[k].w, r);
-      }
+    for (uint32_t k = 0; k < K; ++k) {
+      const uint4 v = in4[i + k * stride];
+      x[4 * k] = v.x;
+      x[4 * k + 1] = v.y;
+      x[4 * k + 2] = v.z;
+      x[4 * k + 3] = v.w;
     }
+    rounds(x, R);
 #pragma unroll
-    for (uint32_t k = 0; k < K; ++k) out4[i + k * stride] = v[k];
+    for (uint32_t k = 0; k < K; ++k)
+      out4[i + k * stride] = make_uint4(x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]);
   }
 
   template <class Bar>
-  __device__ static void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
+  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const MixArgs& a = dt.mix;
     const uint32_t gl = p.wg * p.nlanes + p.lane;
     const uint32_t stride = p.nwg * p.nlanes;
@@ -496,7 +539,7 @@ struct LdsHist {
   }
 
   template <class Bar>
-  __device__ static void run(const DevTask& dt, const Part& p, Bar& bar, uint32_t* lds) {
+  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar& bar, uint32_t* lds) {
     const HistArgs& a = dt.hist;
     const uint32_t lane = lane_id();
     for (uint32_t i = p.lane; i < 256u * kCopies; i += p.nlanes) lds[i] = 0u;
@@ -616,7 +659,7 @@ struct Im2col {
   static constexpr uint32_t lds_words(int) { return 0; }
   static constexpr uint32_t kStep = 3;
 
-  __device__ static void run_rows(const Im2colArgs& a, const Part& p, uint32_t lane) {
+  __device__ static __forceinline__ void run_rows(const Im2colArgs& a, const Part& p, uint32_t lane) {
     const uint32_t nw = p.nwg * p.nwaves;
     const uint32_t gw = p.wg * p.nwaves + p.wave;
     const uint32_t per = (a.row_units + nw - 1u) / nw;  // units of the busiest wavefront
@@ -673,7 +716,7 @@ struct Im2col {
   }
 
   template <class Bar>
-  __device__ static void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
+  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const Im2colArgs& a = dt.im2col;
     const uint32_t lane = lane_id();
     if (a.row3) {
@@ -768,7 +811,7 @@ struct Upsample {
     float e[kBand + 2];
   };
 
-  __device__ static void run_rows(const UpArgs& a, const Part& p, uint32_t lane) {
+  __device__ static __forceinline__ void run_rows(const UpArgs& a, const Part& p, uint32_t lane) {
     const uint32_t nw = p.nwg * p.nwaves;
     const uint32_t W = a.W, HW = a.H * a.W, OHW = a.Ho * a.Wo;
     const uint32_t qrow = lane >> 4, c4 = lane & 15u;
@@ -854,7 +897,7 @@ struct Upsample {
   }
 
   template <class Bar>
-  __device__ static void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
+  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const UpArgs& a = dt.up;
     const uint32_t lane = lane_id();
     if (a.row2) {
@@ -944,7 +987,7 @@ struct Maxpool {
     }
   }
 
-  __device__ static void run_rows(const PoolArgs& a, const Part& p, uint32_t lane) {
+  __device__ static __forceinline__ void run_rows(const PoolArgs& a, const Part& p, uint32_t lane) {
     const uint32_t nw = p.nwg * p.nwaves;
     const uint32_t gw = p.wg * p.nwaves + p.wave;
     const uint32_t W = a.W, HW = a.H * a.W, OHW = a.Ho * a.Wo;
@@ -1050,7 +1093,7 @@ struct Maxpool {
   }
 
   template <class Bar>
-  __device__ static void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
+  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const PoolArgs& a = dt.pool;
     const uint32_t lane = lane_id();
     if (a.row3) {

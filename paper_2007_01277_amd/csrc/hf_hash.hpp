@@ -11,6 +11,30 @@
 
 namespace hf {
 
+// Three-input bitwise functions as one v_bitop3_b32 each: the truth table TT
+// gives the result for (a, b, c) at bit 4a + 2b + c.  The compiler forms them for
+// some expressions only (of a SHA-256 round's xors of three rotations it made two
+// xors each, 1578 in all).  Where a word is known at compile time (padding) the
+// plain expression stays, which folds.
+constexpr int kXor3 = 0x96, kCh = 0xCA, kMaj = 0xE8;
+template <int TT>
+__device__ __forceinline__ uint32_t op3(uint32_t a, uint32_t b, uint32_t c) {
+  if (__builtin_constant_p(a) || __builtin_constant_p(b) || __builtin_constant_p(c))
+    return TT == kXor3 ? a ^ b ^ c : TT == kCh ? (a & b) ^ (~a & c) : (a & b) ^ (a & c) ^ (b & c);
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, TT);
+}
+// A 64-bit word from its halves as a register pair (an or of a shifted half would
+// be split up again and added half by half).
+__device__ __forceinline__ uint64_t pair64(uint32_t lo, uint32_t hi) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint64_t, (u32x2){lo, hi});
+}
+template <int TT>
+__device__ __forceinline__ uint64_t op3(uint64_t a, uint64_t b, uint64_t c) {
+  return pair64(op3<TT>((uint32_t)a, (uint32_t)b, (uint32_t)c),
+                op3<TT>((uint32_t)(a >> 32), (uint32_t)(b >> 32), (uint32_t)(c >> 32)));
+}
+
 // 64-bit rotate and shift right by a compile-time amount (SHA-512).  A value
 // that differs between lanes (uni false) takes one funnel shift
 // (v_alignbit_b32) per 32-bit half, where the compiler's own lowering of a
@@ -22,26 +46,30 @@ __device__ __forceinline__ uint64_t rotr64(uint64_t x, uint32_t n, bool uni = fa
   if (uni) return __builtin_rotateright64(x, n);
   const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
   uint32_t rl, rh;
-  if (n < 32) {
+  if (n == 32) {
+    rl = hi;
+    rh = lo;
+  } else if (n < 32) {
     rl = __builtin_amdgcn_alignbit(hi, lo, n);
     rh = __builtin_amdgcn_alignbit(lo, hi, n);
   } else {
     rl = __builtin_amdgcn_alignbit(lo, hi, n - 32);
     rh = __builtin_amdgcn_alignbit(hi, lo, n - 32);
   }
-  return ((uint64_t)rh << 32) | rl;
+  return pair64(rl, rh);
 }
 __device__ __forceinline__ uint64_t shr64(uint64_t x, uint32_t n, bool uni = false) {  // 0 < n < 32
   if (uni) return x >> n;
   const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
-  return ((uint64_t)(hi >> n) << 32) | __builtin_amdgcn_alignbit(hi, lo, n);
+  return pair64(__builtin_amdgcn_alignbit(hi, lo, n), hi >> n);
 }
 
 // ============================================================ SHA-256d
 // FIPS 180-4.  The first 64 header bytes are the same for every nonce, so their
 // compression (the midstate) is computed once per wavefront from uniform
 // values; each lane then compresses the second block of its message and hashes
-// the 32-byte digest again.
+// the 32-byte digest again.  Bound by VALU issue: 2^22 nonces 358 us with the
+// compiler's xors, 288 us with one v_bitop3 per three-input function (op3).
 struct Sha256d {
   static constexpr uint32_t lds_words(int) { return 0; }
 
@@ -64,7 +92,9 @@ struct Sha256d {
   // Sec. 6.2.2, rounds t0 .. t0+15 on the working variables; w is the rolling
   // 16-word message schedule (FIRST: rounds 0..15 read the block itself).
   // Within a chunk every schedule index is a compile-time constant.
-  template <bool FIRST>
+  // UNI: the first UNI rounds see wave-uniform values only and keep the plain
+  // form, which the scalar unit executes (a vector instruction would not be).
+  template <bool FIRST, int UNI>
   __device__ static __forceinline__ void chunk(uint32_t (&v)[8], uint32_t (&w)[16], int t0) {
     uint32_t a = v[0], b = v[1], c = v[2], d = v[3], e = v[4], f = v[5], g = v[6], h = v[7];
 #pragma unroll
@@ -74,16 +104,24 @@ struct Sha256d {
         wt = w[i];
       } else {
         const uint32_t x = w[(i + 1) & 15], y = w[(i + 14) & 15];
-        const uint32_t s0 = rotr(x, 7) ^ rotr(x, 18) ^ (x >> 3);
-        const uint32_t s1 = rotr(y, 17) ^ rotr(y, 19) ^ (y >> 10);
+        const uint32_t s0 = op3<kXor3>(rotr(x, 7), rotr(x, 18), x >> 3);
+        const uint32_t s1 = op3<kXor3>(rotr(y, 17), rotr(y, 19), y >> 10);
         wt = s1 + w[(i + 9) & 15] + s0 + w[i];
         w[i] = wt;
       }
-      const uint32_t S1 = rotr(e, 6) ^ rotr(e, 11) ^ rotr(e, 25);
-      const uint32_t ch = (e & f) ^ (~e & g);
+      uint32_t S1, ch, S0, maj;
+      if (t0 + i < UNI) {
+        S1 = rotr(e, 6) ^ rotr(e, 11) ^ rotr(e, 25);
+        ch = (e & f) ^ (~e & g);
+        S0 = rotr(a, 2) ^ rotr(a, 13) ^ rotr(a, 22);
+        maj = (a & b) ^ (a & c) ^ (b & c);
+      } else {
+        S1 = op3<kXor3>(rotr(e, 6), rotr(e, 11), rotr(e, 25));
+        ch = op3<kCh>(e, f, g);
+        S0 = op3<kXor3>(rotr(a, 2), rotr(a, 13), rotr(a, 22));
+        maj = op3<kMaj>(a, b, c);
+      }
       const uint32_t T1 = h + S1 + ch + kK[t0 + i] + wt;
-      const uint32_t S0 = rotr(a, 2) ^ rotr(a, 13) ^ rotr(a, 22);
-      const uint32_t maj = (a & b) ^ (a & c) ^ (b & c);
       const uint32_t T2 = S0 + maj;
       h = g;
       g = f;
@@ -107,23 +145,23 @@ struct Sha256d {
   // one block into the state st (Sec. 6.2.2): four unrolled 16-round chunks.
   // The constant words of a padded block fold into the schedule, and writing
   // the rounds as chunks over one 16-word schedule array (rather than as one
-  // 64-round loop) keeps the compiler's live ranges short: the same 3139
-  // instructions per nonce in 51 VGPRs instead of 79, so a fused kernel can
-  // hold 8 waves per SIMD without spilling.
+  // 64-round loop) keeps the compiler's live ranges short: 48 VGPRs, so a fused
+  // kernel can hold 8 waves per SIMD without spilling.
+  template <int UNI>
   __device__ static __forceinline__ void compress(uint32_t (&st)[8], uint32_t (&w)[16]) {
     uint32_t v[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) v[k] = st[k];
-    chunk<true>(v, w, 0);
-    chunk<false>(v, w, 16);
-    chunk<false>(v, w, 32);
-    chunk<false>(v, w, 48);
+    chunk<true, UNI>(v, w, 0);
+    chunk<false, UNI>(v, w, 16);
+    chunk<false, UNI>(v, w, 32);
+    chunk<false, UNI>(v, w, 48);
 #pragma unroll
     for (int k = 0; k < 8; ++k) st[k] += v[k];
   }
 
   template <class Bar>
-  __device__ static void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
+  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const ShaArgs& a = dt.sha;
     if (a.n == 0) return;
     // midstate of the first 64 bytes (big-endian words, Sec. 5.2.1); the
@@ -134,7 +172,7 @@ struct Sha256d {
     for (int k = 0; k < 8; ++k) mid[k] = kH0[k];
 #pragma unroll
     for (int k = 0; k < 16; ++k) w[k] = __builtin_bswap32(a.hdr[k]);
-    compress(mid, w);
+    compress<0>(mid, w);
     // uniform across the wavefront: scalar registers, not VGPRs
 #pragma unroll
     for (int k = 0; k < 8; ++k) mid[k] = uniform(mid[k]);
@@ -148,14 +186,14 @@ struct Sha256d {
       for (int k = 0; k < 8; ++k) st[k] = mid[k];
       uint32_t m[16] = {t16, t17, t18, __builtin_bswap32(a.nonce0 + i), 0x80000000u, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0,
                         640u};
-      compress(st, m);
+      compress<3>(st, m);  // word 3 is the first that differs
       // second hash: the 32-byte digest, padded
       uint32_t s2[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) s2[k] = kH0[k];
       uint32_t m2[16] = {st[0], st[1], st[2], st[3], st[4], st[5], st[6], st[7], 0x80000000u, 0, 0, 0, 0, 0, 0,
                          256u};
-      compress(s2, m2);
+      compress<0>(s2, m2);
       uint4* o = reinterpret_cast<uint4*>(a.out + 8u * i);
       o[0] = make_uint4(__builtin_bswap32(s2[0]), __builtin_bswap32(s2[1]), __builtin_bswap32(s2[2]),
                         __builtin_bswap32(s2[3]));
@@ -167,6 +205,9 @@ struct Sha256d {
 
 // ============================================================ BLAKE2b
 // RFC 7693, 32-byte digest, no key: the 80-byte message is one padded block.
+// Bound by VALU issue: 2^22 nonces 219 us with the compiler's rotations (two
+// 64-bit shifts and two ors, or parts of them), 190 us with one v_alignbit per
+// half (rotr64).
 // Message words 0..8 are the same for every nonce; word 9 carries the nonce.
 struct Blake2b {
   static constexpr uint32_t lds_words(int) { return 0; }
@@ -184,22 +225,23 @@ struct Blake2b {
       {6, 15, 14, 9, 11, 3, 0, 8, 12, 2, 13, 7, 1, 4, 10, 5}, {10, 2, 8, 4, 7, 6, 1, 5, 15, 11, 9, 14, 3, 12, 13, 0},
       {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15}, {14, 10, 4, 8, 9, 15, 13, 6, 1, 12, 0, 2, 11, 7, 5, 3}};
 
-  __device__ static __forceinline__ uint64_t rotr(uint64_t x, uint32_t n) { return __builtin_rotateright64(x, n); }
-
-  // Sec. 3.1
-  __device__ static __forceinline__ void G(uint64_t (&v)[16], int a, int b, int c, int d, uint64_t x, uint64_t y) {
+  // Sec. 3.1.  u1, u2: the words of the first (second) half are wave-uniform, as
+  // in round 0 all are until message word 9 enters: those rotations keep the
+  // scalar form, or 32 loop-invariant values would sit in vector registers.
+  __device__ static __forceinline__ void G(uint64_t (&v)[16], int a, int b, int c, int d, uint64_t x, uint64_t y,
+                                           bool u1 = false, bool u2 = false) {
     v[a] = v[a] + v[b] + x;
-    v[d] = rotr(v[d] ^ v[a], 32);
+    v[d] = rotr64(v[d] ^ v[a], 32, u1);
     v[c] = v[c] + v[d];
-    v[b] = rotr(v[b] ^ v[c], 24);
+    v[b] = rotr64(v[b] ^ v[c], 24, u1);
     v[a] = v[a] + v[b] + y;
-    v[d] = rotr(v[d] ^ v[a], 16);
+    v[d] = rotr64(v[d] ^ v[a], 16, u2);
     v[c] = v[c] + v[d];
-    v[b] = rotr(v[b] ^ v[c], 63);
+    v[b] = rotr64(v[b] ^ v[c], 63, u2);
   }
 
   template <class Bar>
-  __device__ static void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
+  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const ShaArgs& a = dt.sha;
     if (a.n == 0) return;
     uint64_t m[16];
@@ -223,14 +265,15 @@ struct Blake2b {
       v[14] = ~v[14];
 #pragma unroll
       for (int r = 0; r < 12; ++r) {
-        G(v, 0, 4, 8, 12, m[kSigma[r][0]], m[kSigma[r][1]]);
-        G(v, 1, 5, 9, 13, m[kSigma[r][2]], m[kSigma[r][3]]);
-        G(v, 2, 6, 10, 14, m[kSigma[r][4]], m[kSigma[r][5]]);
-        G(v, 3, 7, 11, 15, m[kSigma[r][6]], m[kSigma[r][7]]);
-        G(v, 0, 5, 10, 15, m[kSigma[r][8]], m[kSigma[r][9]]);
-        G(v, 1, 6, 11, 12, m[kSigma[r][10]], m[kSigma[r][11]]);
-        G(v, 2, 7, 8, 13, m[kSigma[r][12]], m[kSigma[r][13]]);
-        G(v, 3, 4, 9, 14, m[kSigma[r][14]], m[kSigma[r][15]]);
+        const bool u = r == 0;  // word 9 is the second of the fifth mixing of round 0
+        G(v, 0, 4, 8, 12, m[kSigma[r][0]], m[kSigma[r][1]], u, u);
+        G(v, 1, 5, 9, 13, m[kSigma[r][2]], m[kSigma[r][3]], u, u);
+        G(v, 2, 6, 10, 14, m[kSigma[r][4]], m[kSigma[r][5]], u, u);
+        G(v, 3, 7, 11, 15, m[kSigma[r][6]], m[kSigma[r][7]], u, u);
+        G(v, 0, 5, 10, 15, m[kSigma[r][8]], m[kSigma[r][9]], u, false);
+        G(v, 1, 6, 11, 12, m[kSigma[r][10]], m[kSigma[r][11]], u, u);
+        G(v, 2, 7, 8, 13, m[kSigma[r][12]], m[kSigma[r][13]], u, u);
+        G(v, 3, 4, 9, 14, m[kSigma[r][14]], m[kSigma[r][15]], u, u);
       }
       uint64_t h[4];
 #pragma unroll
@@ -281,6 +324,10 @@ struct Sha512 {
     return j <= 8 || (j >= 10 && j <= 15) || j == 17 || j == 19 || j == 21;
   }
 
+  __device__ static __forceinline__ uint64_t xor3(uint64_t a, uint64_t b, uint64_t c, bool uniform_words) {
+    return uniform_words ? a ^ b ^ c : op3<kXor3>(a, b, c);
+  }
+
   // Sec. 6.4.2, rounds T0 .. T1-1 on the working variables v; w is the rolling
   // 16-word schedule (rounds below 16 read the block itself).  Every index is a
   // compile-time constant once the loop is unrolled.  Rounds below 9 see only
@@ -301,8 +348,8 @@ struct Sha512 {
         const int i = t & 15;
         const uint64_t x = w[(i + 1) & 15], y = w[(i + 14) & 15];
         const bool ux = uni(t - 15), uy = uni(t - 2);
-        const uint64_t s0 = rotr64(x, 1, ux) ^ rotr64(x, 8, ux) ^ shr64(x, 7, ux);
-        const uint64_t s1 = rotr64(y, 19, uy) ^ rotr64(y, 61, uy) ^ shr64(y, 6, uy);
+        const uint64_t s0 = xor3(rotr64(x, 1, ux), rotr64(x, 8, ux), shr64(x, 7, ux), ux);
+        const uint64_t s1 = xor3(rotr64(y, 19, uy), rotr64(y, 61, uy), shr64(y, 6, uy), uy);
         const uint64_t q = w[(i + 9) & 15], r = w[i];
         const bool uq = uni(t - 7), ur = uni(t - 16);
         const uint64_t wu = (uy ? s1 : 0) + (uq ? q : 0) + (ux ? s0 : 0) + (ur ? r : 0);
@@ -310,11 +357,11 @@ struct Sha512 {
         ku = kK[t] + wu;
         w[i] = wu + wv;
       }
-      const uint64_t S1 = rotr64(e, 14, us) ^ rotr64(e, 18, us) ^ rotr64(e, 41, us);
-      const uint64_t ch = (e & f) ^ (~e & g);
+      const uint64_t S1 = xor3(rotr64(e, 14, us), rotr64(e, 18, us), rotr64(e, 41, us), us);
+      const uint64_t ch = us ? (e & f) ^ (~e & g) : op3<kCh>(e, f, g);
       const uint64_t T1v = ku + h + S1 + ch + wv;
-      const uint64_t S0 = rotr64(a, 28, us) ^ rotr64(a, 34, us) ^ rotr64(a, 39, us);
-      const uint64_t ab = a ^ b, maj = (ab & c) | (~ab & a);  // a where a == b, else c
+      const uint64_t S0 = xor3(rotr64(a, 28, us), rotr64(a, 34, us), rotr64(a, 39, us), us);
+      const uint64_t maj = us ? (a & b) ^ (a & c) ^ (b & c) : op3<kMaj>(a, b, c);
       h = g;
       g = f;
       f = e;
@@ -350,6 +397,9 @@ struct Sha512 {
 // the last instance and store nothing, so every lane takes part in every
 // permute.
 struct EthashLike {
+  // 78 VGPRs alone; next to some bodies the compiler takes 104 and four waves per
+  // SIMD (with sha256d, split 6 of 8, block 512: 708 us; at six waves 559)
+  static constexpr int kFusedWaves = 6;
   static constexpr uint32_t lds_words(int) { return 0; }
   static constexpr uint32_t kPrime = 16777619u;
   static constexpr uint32_t kChains = 4;
@@ -364,7 +414,7 @@ struct EthashLike {
   }
 
   template <class Bar>
-  __device__ static void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
+  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const EthArgs& a = dt.eth;
     if (a.n == 0) return;
     // rounds 0..8 read header words only: uniform, so scalar registers

@@ -737,22 +737,23 @@ __global__ void __launch_bounds__(256) k_zero_words(uint32_t* __restrict__ p, ui
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0u;
 }
 
-// The integer-issue ceiling: the int_mix round on four independent chains per
-// lane, as the int_mix body runs it, from registers only (no memory traffic
-// in the loop), so its rate is what the VALU sustains for this instruction mix.
+// The integer-issue ceiling: the int_mix rounds on kPeakChains independent chains
+// per lane, as the int_mix body runs them on a step of four vectors, from
+// registers only (no memory traffic in the loop), so its rate is what the VALU
+// sustains for this instruction mix.
+constexpr uint32_t kPeakChains = 16;
+
 __global__ void __launch_bounds__(256) k_int_peak(uint32_t* sink, uint32_t rounds) {
-  // every chain starts from a per-lane value, so all four stay vector
-  // registers (a wave-uniform start would let the compiler run a chain on the
-  // scalar unit)
-  uint32_t a = threadIdx.x, b = threadIdx.x * 977u + blockIdx.x, c = threadIdx.x ^ 0x5555u,
-           d = (threadIdx.x << 8) ^ blockIdx.x;
-  for (uint32_t r = 0; r < rounds; ++r) {
-    a = IntMix::round1(a, r);
-    b = IntMix::round1(b, r);
-    c = IntMix::round1(c, r);
-    d = IntMix::round1(d, r);
-  }
-  if ((a ^ b ^ c ^ d) == 0x12345678u) sink[blockIdx.x % kSinkWords] = a;  // keeps the loop alive
+  // every chain starts from a per-lane value, so all stay vector registers (a
+  // wave-uniform start would let the compiler run a chain on the scalar unit)
+  uint32_t x[kPeakChains];
+#pragma unroll
+  for (uint32_t k = 0; k < kPeakChains; ++k) x[k] = (threadIdx.x * (977u + 2u * k)) ^ (blockIdx.x + k);
+  IntMix::rounds(x, rounds);
+  uint32_t v = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kPeakChains; ++k) v ^= x[k];
+  if (v == 0x12345678u) sink[blockIdx.x % kSinkWords] = v;  // keeps the loop alive
 }
 
 __global__ void __launch_bounds__(256) k_spin(uint32_t* sink, uint32_t iters) {
@@ -1080,7 +1081,7 @@ int hf_int_peak(int rounds, int grid, void* stream, float* ms_out, double* lane_
   hipLaunchKernelGGL(k_int_peak, dim3(grid), dim3(256), 0, st, static_cast<uint32_t*>(s->warm), (uint32_t)rounds);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return record_hip(e);
-  if (lane_ops_out) *lane_ops_out = 8.0 * 4.0 * 256.0 * (double)grid * (double)rounds;
+  if (lane_ops_out) *lane_ops_out = 8.0 * kPeakChains * 256.0 * (double)grid * (double)rounds;
   return timed_end(s, st, ms_out);
 }
 

@@ -74,3 +74,13 @@ def test_fused_bodies_with_grids_of_their_own(cfg):
             if ca is not cb:
                 pr = H.make_pair(ca.task, cb.task)
                 G.run_and_check(lambda: H.hf_run_fused_cfg(pr, H.hf_config(*cfg, 0)), [ca, cb])
+
+
+@pytest.mark.parametrize("n", [4, 63, 64, 255, 256, 257, 1023, 1025, 5000])
+@pytest.mark.parametrize("rounds", [0, 1, 2, 7])
+def test_int_mix_steps_of_one_to_four_vectors(n, rounds):
+    """One lane takes one, two, three or four vectors per step (few workgroups
+    make the steps full), with and without a scalar tail."""
+    c = G.mix_case(n, rounds, seed=n + rounds)
+    for grid in (1, 2, 0):
+        G.run_and_check(lambda: H.hf_run_solo(c.task, 256, grid), [c])
