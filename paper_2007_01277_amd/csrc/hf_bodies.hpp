@@ -56,10 +56,10 @@ struct Im2colArgs {  // patches -> columns, [N][C*kh*kw][Ho*Wo]
   const float* x;
   float* out;
   uint32_t C, H, W, kw, s, p, Ho, Wo, KK;
-  uint32_t units;           // N * C * kh*kw output planes
-  uint32_t lanes_per_unit;  // Ho * Wo4 (vector) or Ho * Wo (scalar)
+  uint32_t elems;           // N * C * H * W
+  uint32_t items;           // N * C * kh * Ho * (Wo4 or Wo): places of the general path
   uint32_t vec;             // Wo % 4 == 0 and out 16-byte aligned
-  FastDiv div_kk, div_row, div_kw;  // div_row: by Wo4 (vector) or Wo
+  FastDiv div_group, div_kh, div_row;  // by Ho * rowlen, kh, and rowlen = Wo4 (vector) or Wo
   uint32_t row3;            // the 3x3 / stride 1 / pad 1 row path (see Im2col)
   uint32_t nch;             // row path: chunks of 64 columns per row, ceil(W / 64)
   uint32_t nq;              // row path: units per channel, ceil(H * nch / 4)
@@ -78,6 +78,9 @@ struct UpArgs {  // bilinear upsampling by integer factor s, half-pixel centres
   uint32_t lanes_per_unit;  // rows_per_unit * Wo4 (vector) or * Wo
   uint32_t vec;             // Wo % 4 == 0 and out 16-byte aligned
   FastDiv div_ho, div_row;  // div_row: by Wo4 (vector) or Wo
+  uint32_t s;
+  uint32_t places;          // the path by places (see Upsample): N * C * H * (Wo4 or Wo), or 0
+  FastDiv div_group;        // by H * (Wo4 or Wo)
   uint32_t row2;            // the scale-2 row path (see Upsample)
   uint32_t nch;             // row path: chunks of 32 input columns per row, ceil(W / 32)
   uint32_t nq;              // row path: units per plane, ceil(bands * nch / 4)
@@ -627,11 +630,19 @@ struct LdsHist {
 
 // ================================================================== im2col
 // Im2Col (Sec. IV-A): out[n][(c*kh + i)*kw + j][oh*Wo + ow] = x[n][c][oh*s-p+i][ow*s-p+j],
-// zero outside the image.  A unit is one output plane (n, c*kh*kw + kk): Ho*Wo
-// contiguous floats, written front to back (float4 when Wo % 4 == 0), so every
-// store instruction covers whole aligned cache lines.  Kernel offsets kk are the
-// fastest-varying unit index, so the kh*kw planes that read one input plane run
-// next to each other and find it in cache.
+// zero outside the image.
+//
+// General path: a place is (n, c, kernel row i, output row, four outputs or one);
+// the places of a wavefront are 64 consecutive ones, so a plane of any size fills
+// its lanes.  A lane reads the input row's span that its outputs need for kJ
+// kernel columns at once (3s + kJ elements for 4 kJ outputs) and writes the kJ
+// planes.  The span is read whole, in unaligned vector loads, whatever of it lies
+// in the padding or in a neighbouring row, and what lies outside the row is
+// zeroed afterwards; only a wavefront of which some span would leave the tensor
+// reads element by element.  Bound by HBM writes: 7x7 / stride 2 / pad 3 over
+// [32,3,224,224], alone: 112, 136 and 181 us at block 256, 512 and 1024 with a
+// wavefront per output plane (4704 planes for 8192 wavefronts) and one load per
+// output, 44, 46 and 48 us now (236 MB written, 5.9 TB/s).
 //
 // Row path (3x3 kernel, stride 1, pad 1, W % 4 == 0, 16-byte aligned input and
 // output): with stride 1, output plane (i, j) of a channel is the channel
@@ -715,45 +726,70 @@ struct Im2col {
     }
   }
 
+  // V outputs per place, S the stride (0: any, read from the arguments), kernel
+  // columns in blocks of J.
+  template <int V, int S, int J>
+  __device__ static __forceinline__ void run_places(const Im2colArgs& a, const Part& p, uint32_t lane) {
+    const uint32_t nl = 64u * p.nwg * p.nwaves;
+    const uint32_t HW = a.H * a.W, plane = a.Ho * a.Wo;
+    const int s = S > 0 ? S : (int)a.s;
+    // elements of a lane: E runs of R contiguous ones, s apart
+    constexpr int R = S > 0 ? (V - 1) * S + J : J, E = S > 0 ? 1 : V;
+    const uint32_t span = (uint32_t)((E - 1) * s + R);
+    for (uint32_t t0 = 64u * (p.wg * p.nwaves + p.wave); t0 < a.items; t0 += nl) {
+      const uint32_t t = min(t0 + lane, a.items - 1u);  // lanes past the end redo the last place
+      const uint32_t g = fdiv(t, a.div_group), pos = t - g * a.div_group.d;
+      const uint32_t nc = fdiv(g, a.div_kh), i = g - nc * a.div_kh.d;
+      const uint32_t oh = fdiv(pos, a.div_row), col = pos - oh * a.div_row.d;
+      const int ih = (int)(oh * a.s + i) - (int)a.p;
+      const bool rowok = (uint32_t)ih < a.H;
+      const uint32_t row = nc * HW + (rowok ? (uint32_t)ih : 0u) * a.W;
+      float* dst = a.out + ((size_t)nc * a.KK + i * a.kw) * plane + oh * a.Wo + (uint32_t)V * col;
+      for (uint32_t j0 = 0; j0 < a.kw; j0 += (uint32_t)J) {
+        const int iw0 = (int)((uint32_t)V * col * a.s + j0) - (int)a.p;  // column of element 0
+        const uint32_t at = row + (uint32_t)iw0;                         // wraps above the tensor's start
+        float v[E][R];
+        if (__builtin_amdgcn_ballot_w64(at > a.elems || at + span > a.elems) == 0ull) {
+          const float* src = a.x + at;
+#pragma unroll
+          for (int e = 0; e < E; ++e) load_run<R>(src + e * s, v[e]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[e][r] = a.x[row + min((uint32_t)max(iw0 + e * s + r, 0), a.W - 1u)];
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+#pragma unroll
+          for (int r = 0; r < R; ++r) v[e][r] = rowok && (uint32_t)(iw0 + e * s + r) < a.W ? v[e][r] : 0.f;
+        if (t0 + lane < a.items) {
+#pragma unroll
+          for (int j = 0; j < J; ++j) {
+            if (j0 + (uint32_t)j < a.kw) {
+              float* q = dst + (size_t)(j0 + (uint32_t)j) * plane;
+              if constexpr (V == 1) __builtin_nontemporal_store(v[0][j], q);
+              else if constexpr (S > 0) store_nt4(q, v[0][j], v[0][S + j], v[0][2 * S + j], v[0][3 * S + j]);
+              else store_nt4(q, v[0][j], v[1][j], v[2][j], v[3][j]);
+            }
+          }
+        }
+      }
+    }
+  }
+
   template <class Bar>
   __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const Im2colArgs& a = dt.im2col;
     const uint32_t lane = lane_id();
-    if (a.row3) {
-      run_rows(a, p, lane);
-      return;
-    }
-    const uint32_t nw = p.nwg * p.nwaves;
-    const uint32_t HW = a.H * a.W;
-    const uint32_t plane = a.Ho * a.Wo;
-    for (uint32_t u = p.wg * p.nwaves + p.wave; u < a.units; u += nw) {
-      const uint32_t nc = fdiv(u, a.div_kk);  // n*C + c
-      const uint32_t kk = u - nc * a.KK;
-      const uint32_t i = fdiv(kk, a.div_kw);
-      const uint32_t j = kk - i * a.kw;
-      const float* img = a.x + nc * HW;
-      float* dst = a.out + u * plane;  // plane u = (n, c*KK + kk)
-      for (uint32_t t = lane; t < a.lanes_per_unit; t += 64u) {
-        const uint32_t oh = fdiv(t, a.div_row);
-        const uint32_t col = t - oh * a.div_row.d;  // ow4 (vector) or ow (scalar)
-        const int ih = (int)(oh * a.s + i) - (int)a.p;
-        const bool rowok = ih >= 0 && ih < (int)a.H;
-        const float* src = img + (rowok ? ih : 0) * (int)a.W;
-        if (a.vec) {
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int iw = (int)((4u * col + e) * a.s + j) - (int)a.p;
-            v[e] = (rowok && iw >= 0 && iw < (int)a.W) ? src[iw] : 0.f;
-          }
-          store_nt4(dst + oh * a.Wo + 4u * col, v[0], v[1], v[2], v[3]);
-        } else {
-          const int iw = (int)(col * a.s + j) - (int)a.p;
-          __builtin_nontemporal_store((rowok && iw >= 0 && iw < (int)a.W) ? src[iw] : 0.f,
-                                      dst + oh * a.Wo + col);
-        }
-      }
-    }
+    // the block of kernel columns: about the kernel's width, so that little of
+    // the span is read in vain
+    if (a.row3) run_rows(a, p, lane);
+    else if (!a.vec) a.kw > 1u ? run_places<1, 0, 4>(a, p, lane) : run_places<1, 0, 1>(a, p, lane);
+    else if (a.s == 1u) a.kw > 4u ? run_places<4, 1, 8>(a, p, lane)
+                        : a.kw > 1u ? run_places<4, 1, 4>(a, p, lane) : run_places<4, 1, 1>(a, p, lane);
+    else if (a.s == 2u) a.kw > 4u ? run_places<4, 2, 8>(a, p, lane) : run_places<4, 2, 4>(a, p, lane);
+    else run_places<4, 0, 4>(a, p, lane);
   }
 };
 
@@ -886,6 +922,70 @@ struct Upsample {
     store(u, cur);
   }
 
+  // Path by places (any other scale; not float4 stores below scale 3): a place is
+  // a plane, a group of the s output rows s*g .. s*g+s-1, and four adjacent output
+  // columns (V = 4) or one.  Its rows lie between three consecutive input rows,
+  // its columns between NC consecutive input columns: V = 1 two, V = 4 three from
+  // scale 4 on and four at scale 3, where rounding can put the first column
+  // left and the last right of an input position.  A lane reads 3 NC inputs for
+  // 4 s outputs, interpolates the three rows horizontally once, and combines them
+  // for every output row.  Every output keeps its own coordinates (coord) and
+  // expressions, so the bits are those of the pointwise path.  x4 over
+  // [16,32,65,65], alone: 58 us pointwise (16 reads and eight coordinates per four
+  // outputs, and 65 float4 of a row taken in two steps of 64 lanes), 37 us
+  // now (147 MB; rows of 1040 bytes leave partial lines); x3 over [16,32,64,64]: 44
+  // and 14 us (87 MB, 6.1 TB/s).
+  template <int V, int NC>
+  __device__ static __forceinline__ void run_places(const UpArgs& a, const Part& p, uint32_t lane) {
+    const uint32_t nl = 64u * p.nwg * p.nwaves;
+    const uint32_t HW = a.H * a.W, OHW = a.Ho * a.Wo;
+    for (uint32_t t0 = 64u * (p.wg * p.nwaves + p.wave); t0 < a.places; t0 += nl) {
+      const uint32_t t = min(t0 + lane, a.places - 1u);  // lanes past the end redo the last place
+      const uint32_t plane = fdiv(t, a.div_group), pos = t - plane * a.div_group.d;
+      const uint32_t g = fdiv(pos, a.div_row), col = (uint32_t)V * (pos - g * a.div_row.d);
+      uint32_t x0[V], x1, yb, y1;
+      float lx[V], ly;
+#pragma unroll
+      for (int c = 0; c < V; ++c) coord(col + (uint32_t)c, a.inv_s, a.W, x0[c], x1, lx[c]);
+      coord(a.s * g, a.inv_s, a.H, yb, y1, ly);
+      const float* img = a.x + (size_t)plane * HW;
+      float in[3][NC];
+#pragma unroll
+      for (uint32_t k = 0; k < 3u; ++k)
+#pragma unroll
+        for (uint32_t c = 0; c < (uint32_t)NC; ++c)
+          in[k][c] = img[min(yb + k, a.H - 1u) * a.W + min(x0[0] + c, a.W - 1u)];
+      float h[3][V];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+          const uint32_t d = x0[c] - x0[0];  // 0 .. NC - 2
+          float l = in[k][0], r = in[k][1];
+#pragma unroll
+          for (uint32_t e = 1; e + 1u < (uint32_t)NC; ++e) {
+            l = d == e ? in[k][e] : l;
+            r = d == e ? in[k][e + 1] : r;
+          }
+          h[k][c] = lerp(l, r, lx[c]);
+        }
+      float* dst = a.out + (size_t)plane * OHW + a.s * g * a.Wo + col;
+      const bool live = t0 + lane < a.places;
+      for (uint32_t r = 0; r < a.s; ++r) {
+        uint32_t y0;
+        coord(a.s * g + r, a.inv_s, a.H, y0, y1, ly);
+        const bool up = y0 != yb;  // then y0 == yb + 1
+        float v[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) v[c] = lerp(up ? h[1][c] : h[0][c], up ? h[2][c] : h[1][c], ly);
+        if (live) {
+          if constexpr (V == 4) store_nt4(dst + r * a.Wo, v[0], v[1], v[2], v[3]);
+          else __builtin_nontemporal_store(v[0], dst + r * a.Wo);
+        }
+      }
+    }
+  }
+
   __device__ static __forceinline__ float sample(const float* r0, const float* r1, float ly, uint32_t W,
                                                  uint32_t ox, float inv_s) {
     uint32_t x0, x1;
@@ -902,6 +1002,12 @@ struct Upsample {
     const uint32_t lane = lane_id();
     if (a.row2) {
       run_rows(a, p, lane);
+      return;
+    }
+    if (a.places) {
+      if (!a.vec) run_places<1, 2>(a, p, lane);
+      else if (a.s == 3u) run_places<4, 4>(a, p, lane);
+      else run_places<4, 3>(a, p, lane);
       return;
     }
     const uint32_t nw = p.nwg * p.nwaves;
@@ -1045,13 +1151,27 @@ struct Maxpool {
 
   __device__ static __forceinline__ int32_t clampi(int32_t v, int32_t hi) { return min(max(v, 0), hi); }
 
-  template <int KH, int KW>
+  // PAD false: no padding, so every window lies in the image and a row of it is
+  // one unaligned vector load instead of a clamp and a load per element
+  // (3x3 / stride 2 over [32,96,111,111], alone: 72 -> 41 us; 2x2: 48 -> 40).
+  template <int KH, int KW, bool PAD>
   __device__ static __forceinline__ void window(const PoolArgs& a, const float* img, int32_t h0, int32_t w0,
                                                 uint32_t kh, uint32_t kw, float& best, int32_t& at) {
     const int32_t Hm = (int32_t)a.H - 1, Wm = (int32_t)a.W - 1, W = (int32_t)a.W;
     const uint32_t nh = KH > 0 ? (uint32_t)KH : kh, nw = KW > 0 ? (uint32_t)KW : kw;
     best = 0.f;
     at = -1;
+    if constexpr (!PAD) {
+      const int32_t e0 = h0 * W + w0;
+      float v[KH][KW];
+#pragma unroll
+      for (int i = 0; i < KH; ++i) load_run<KW>(img + e0 + i * W, v[i]);
+#pragma unroll
+      for (int i = 0; i < KH; ++i)
+#pragma unroll
+        for (int j = 0; j < KW; ++j) take(v[i][j], e0 + i * W + j, i == 0 && j == 0, best, at);
+      return;
+    }
 #pragma unroll
     for (uint32_t i = 0; i < nh; ++i) {
       const int32_t h = clampi(h0 + (int32_t)i, Hm);
@@ -1067,7 +1187,7 @@ struct Maxpool {
     }
   }
 
-  template <int KH, int KW>
+  template <int KH, int KW, bool PAD>
   __device__ static __forceinline__ void units(const PoolArgs& a, uint32_t ubeg, uint32_t uend, uint32_t lane) {
     const uint32_t plane_sz = a.H * a.W;
     for (uint32_t u = ubeg; u < uend; ++u) {
@@ -1082,7 +1202,7 @@ struct Maxpool {
         const float* img = a.x + (size_t)plane * plane_sz;
         float best;
         int32_t at;
-        window<KH, KW>(a, img, (int32_t)(oh * a.s) - (int32_t)a.p, (int32_t)(ow * a.s) - (int32_t)a.p, a.kh,
+        window<KH, KW, PAD>(a, img, (int32_t)(oh * a.s) - (int32_t)a.p, (int32_t)(ow * a.s) - (int32_t)a.p, a.kh,
                        a.kw, best, at);
         if (o < a.total) {
           __builtin_nontemporal_store(best, a.out + o);
@@ -1107,11 +1227,11 @@ struct Maxpool {
     const uint32_t uend = ubeg + q + (gw < r ? 1u : 0u);
     if (ubeg >= uend) return;
     if (a.kh == 3 && a.kw == 3)
-      units<3, 3>(a, ubeg, uend, lane);
+      a.p ? units<3, 3, true>(a, ubeg, uend, lane) : units<3, 3, false>(a, ubeg, uend, lane);
     else if (a.kh == 2 && a.kw == 2)
-      units<2, 2>(a, ubeg, uend, lane);
+      a.p ? units<2, 2, true>(a, ubeg, uend, lane) : units<2, 2, false>(a, ubeg, uend, lane);
     else
-      units<0, 0>(a, ubeg, uend, lane);
+      units<0, 0, true>(a, ubeg, uend, lane);
   }
 };
 

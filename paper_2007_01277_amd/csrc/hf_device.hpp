@@ -40,6 +40,29 @@ __device__ __forceinline__ uint32_t uniform(uint32_t v) {
 // ----------------------------------------------------------------- streaming stores
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// N consecutive floats from a 4-byte aligned address, in the widest loads (the
+// vector-memory unit takes any dword alignment).
+template <int N>
+__device__ __forceinline__ void load_run(const float* p, float (&v)[N]) {
+  typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+  typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+  constexpr int Q = N / 4 * 4;
+#pragma unroll
+  for (int k = 0; k < Q; k += 4) {
+    const f32x4u q = *reinterpret_cast<const f32x4u*>(p + k);
+    v[k] = q.x;
+    v[k + 1] = q.y;
+    v[k + 2] = q.z;
+    v[k + 3] = q.w;
+  }
+  if constexpr ((N & 2) != 0) {
+    const f32x2u q = *reinterpret_cast<const f32x2u*>(p + Q);
+    v[Q] = q.x;
+    v[Q + 1] = q.y;
+  }
+  if constexpr ((N & 1) != 0) v[N - 1] = p[N - 1];
+}
+
 // 16-byte store with the non-temporal hint: output that is written once and
 // not read back by the kernel should not displace inputs from the caches.
 __device__ __forceinline__ void store_nt4(float* p, float a, float b, float c, float d) {

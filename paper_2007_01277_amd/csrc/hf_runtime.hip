@@ -344,13 +344,13 @@ int prepare(const hf_task* t, void* scratch, bool own, DevTask* dt) {
       a.Ho = (a.H + 2 * p - kh) / s + 1;
       a.Wo = (a.W + 2 * p - kw) / s + 1;
       a.KK = kh * kw;
-      a.units = (uint32_t)t->n * a.C * a.KK;
+      a.elems = (uint32_t)(t->n * t->c * t->h * t->w);
       a.vec = (a.Wo % 4u == 0u) && aligned(t->out0, 16);
       const uint32_t rowlen = a.vec ? a.Wo / 4u : a.Wo;
-      a.lanes_per_unit = a.Ho * rowlen;
-      a.div_kk = make_fastdiv(a.KK);
+      a.items = (uint32_t)t->n * a.C * kh * a.Ho * rowlen;
+      a.div_group = make_fastdiv(a.Ho * rowlen);
+      a.div_kh = make_fastdiv(kh);
       a.div_row = make_fastdiv(rowlen);
-      a.div_kw = make_fastdiv(kw);
       // the row path addresses one plane through a buffer resource of < 2^31 bytes
       a.row3 = kh == 3 && kw == 3 && s == 1 && p == 1 && a.W % 4u == 0u &&
                (uint64_t)a.H * a.W * 4u < (1ull << 31) && aligned(t->in, 16) && aligned(t->out0, 16);
@@ -379,6 +379,14 @@ int prepare(const hf_task* t, void* scratch, bool own, DevTask* dt) {
       a.lanes_per_unit = a.rows_per_unit * rowlen;
       a.div_ho = make_fastdiv(a.Ho);
       a.div_row = make_fastdiv(rowlen);
+      a.s = s;
+      // by places: the coordinates of neighbouring outputs have to keep their
+      // distance, which float32 grants below 2^22; four outputs lie between four
+      // input columns from scale 3 on
+      a.places = (!a.vec || s >= 3u) && a.Ho < (1u << 22) && a.Wo < (1u << 22)
+                     ? (uint32_t)t->n * (uint32_t)t->c * a.H * rowlen
+                     : 0u;
+      a.div_group = make_fastdiv(a.H * rowlen);
       // the row path addresses one input and one output plane through buffer
       // resources of < 2^31 bytes
       a.row2 = s == 2u && a.W % 2u == 0u && (uint64_t)a.Ho * a.Wo * 4u < (1ull << 31) && aligned(t->in, 8) &&
@@ -450,8 +458,8 @@ int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves) {
     case HF_BN_STATS: units = cdiv(d.bn.total, waves); break;
     case HF_INT_MIX: units = cdiv(d.mix.n4 ? d.mix.n4 : d.mix.n, 64 * waves); break;
     case HF_LDS_HIST: units = cdiv(std::max<uint32_t>(d.hist.n16, 1), 64 * waves); break;
-    case HF_IM2COL: units = cdiv(d.im2col.row3 ? d.im2col.row_units : d.im2col.units, waves); break;
-    case HF_UPSAMPLE: units = cdiv(d.up.row2 ? d.up.row_units : d.up.units, waves); break;
+    case HF_IM2COL: units = cdiv(d.im2col.row3 ? d.im2col.row_units : cdiv(d.im2col.items, 64), waves); break;
+    case HF_UPSAMPLE: units = cdiv(d.up.row2 ? d.up.row_units : d.up.places ? cdiv(d.up.places, 64) : d.up.units, waves); break;
     case HF_MAXPOOL: units = cdiv(d.pool.row3 ? d.pool.row_units : d.pool.units, waves); break;
     case HF_SHA256D:
     case HF_BLAKE2B: units = cdiv(d.sha.n, 64 * waves); break;

@@ -84,3 +84,71 @@ def test_int_mix_steps_of_one_to_four_vectors(n, rounds):
     c = G.mix_case(n, rounds, seed=n + rounds)
     for grid in (1, 2, 0):
         G.run_and_check(lambda: H.hf_run_solo(c.task, 256, grid), [c])
+
+
+# kernel, stride, pad: every block width and stride class of im2col's general path
+@pytest.mark.parametrize("k,s,p", [((1, 1), 1, 0), ((1, 1), 2, 0), ((2, 3), 1, 1), ((3, 3), 2, 1), ((4, 4), 1, 2),
+                                   ((4, 4), 4, 0), ((5, 5), 1, 2), ((7, 7), 2, 3), ((3, 9), 2, 4), ((11, 17), 3, 8),
+                                   ((2, 2), 5, 1)])
+@pytest.mark.parametrize("shape", [(1, 1, 11, 16), (2, 3, 12, 17), (3, 1, 19, 28), (1, 2, 40, 65)])
+def test_im2col_general_path(k, s, p, shape):
+    for off in (0, 1):  # one element into its allocation: neither input nor output vector-aligned
+        c = G.im2col_case(shape, k, s, p, seed=sum(shape) + off)
+        if off:
+            x, o = G.dev(inputs.normal_image(shape, sum(shape) + off), 1), c.bufs["outs"][0]
+            o2 = _out(o.shape, 1)
+            c.bufs["outs"] = [o2]
+            c.bufs["in"] = x
+            c.task = H.task_im2col(x, o2, k[0], k[1], s, p)
+        for block, grid in ((256, 0), (1024, 0), (256, 1)):
+            G.run_and_check(lambda: H.hf_run_solo(c.task, block, grid), [c])
+
+
+def _coord32(o, s, length):
+    """The kernel's source coordinate of outputs o, step by step in float32."""
+    f = np.float32
+    t = np.maximum((o.astype(f) + f(0.5)) * (f(1.0) / f(s)) - f(0.5), f(0.0))
+    a = np.minimum(t.astype(np.uint32), length - 1).astype(np.int64)
+    return a, np.minimum(a + 1, length - 1), t - a.astype(f)
+
+
+def _upsample32(x, s):
+    """The pointwise definition in float32, rounding after every operation."""
+    n, c, h, w = x.shape
+    y0, y1, ly = _coord32(np.arange(h * s), s, h)
+    x0, x1, lx = _coord32(np.arange(w * s), s, w)
+
+    def lerp(a, b, l):
+        return a + l * (b - a)
+
+    top = lerp(x[:, :, y0][..., x0], x[:, :, y0][..., x1], lx)
+    bot = lerp(x[:, :, y1][..., x0], x[:, :, y1][..., x1], lx)
+    return lerp(top, bot, ly[:, None])
+
+
+@pytest.mark.parametrize("s", [1, 2, 3, 4, 5, 7, 8, 16])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (2, 3, 5, 4), (1, 2, 9, 33), (3, 1, 2, 68), (1, 1, 65, 65)])
+def test_upsample_by_places_has_the_pointwise_bits(s, shape):
+    xh = inputs.normal_image(shape, 10 * s + shape[3])
+    x = G.dev(xh)
+    want = _upsample32(xh, s)
+    for off in (0, 1):
+        for block, grid in ((256, 0), (512, 1)):
+            o = _out((shape[0], shape[1], shape[2] * s, shape[3] * s), off)
+            got = _run((H.task_upsample(x, o, s), o), block, grid).cpu().numpy()
+            assert np.array_equal(got, want), (off, block, grid)
+
+
+@pytest.mark.parametrize("k,s", [((2, 2), 2), ((2, 2), 1), ((3, 3), 2), ((3, 3), 3)])
+@pytest.mark.parametrize("shape", [(1, 1, 3, 3), (2, 3, 7, 9), (1, 2, 33, 129), (4, 5, 6, 64)])
+@pytest.mark.parametrize("special", [False, True])
+def test_maxpool_without_padding(k, s, shape, special):
+    g = inputs.rng(shape[3] + s)
+    x = np.round(g.standard_normal(shape)).astype(np.float32)  # ties
+    if special:
+        x[g.random(shape) < 0.1] = np.nan
+        x[g.random(shape) < 0.1] = -np.inf
+    for off in (0, 1):
+        c = G.pool_case(shape, k, s, 0, offset=off, x=x)
+        for block in (256, 1024):
+            G.run_and_check(lambda: H.hf_run_solo(c.task, block), [c])

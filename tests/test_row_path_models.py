@@ -284,3 +284,32 @@ def test_upsample2_band_model_gives_the_row_model_s_bits(shape, special):
         x[g.random(shape) < 0.05] = np.nan
     with np.errstate(invalid="ignore"):
         assert np.array_equal(upsample2_bands(x), upsample2_rows(x), equal_nan=True)
+
+
+@pytest.mark.parametrize("s", range(1, 17))
+def test_upsample_places_never_reach_past_their_inputs(s):
+    """What the path by places assumes of the float32 coordinates: four adjacent
+    outputs (a multiple of four first) start in three input columns from scale 4
+    on, in four at scale 3 (one column more than the distance of their lower
+    neighbours); the s rows of a group have two lower neighbours, next to each
+    other.  At every position of short rows and around the largest admitted."""
+    f = np.float32
+
+    def lower(o, length):
+        t = np.maximum((o.astype(f) + f(0.5)) * (f(1.0) / f(s)) - f(0.5), f(0.0))
+        return np.minimum(t.astype(np.uint32), length - 1).astype(np.int64)
+
+    top = (1 << 22) // s
+    for length in (1, 2, 3, 5, 4096, 100_003, top - 1):
+        n = length * s
+        starts = np.arange(0, n, s) if n < 300_000 else np.concatenate([np.arange(0, 30 * s, s),
+                                                                        np.arange(n - 30_000 * s, n, s)])
+        first, last = lower(starts, length), lower(starts + s - 1, length)
+        mid = lower(starts + (s - 1) // 2, length)
+        assert np.all((last - first >= 0) & (last - first <= 1)) and np.all((mid - first >= 0) & (mid <= last))
+        if s >= 3:
+            q = np.arange(0, n - n % 4, 4) if n < 300_000 else np.arange(n // 4 * 4 - 200_000, n // 4 * 4, 4)
+            b = lower(q, length)
+            for e in (1, 2, 3):
+                d = lower(q + e, length) - b
+                assert np.all((d >= 0) & (d <= (2 if s == 3 else 1)))
