@@ -59,10 +59,27 @@ static std::vector<KernelEntry>& registry() {
   return all;
 }
 
+// Place of a (kind a, kind b or solo, block, cap) in a flat table, or -1.
+static int entry_index(int ka, int kb, int block, int cap) {
+  const int b = block == 256 ? 0 : block == 512 ? 1 : block == 1024 ? 2 : -1;
+  const int c = cap == 0 ? 0 : cap == 64 ? 1 : cap == 80 ? 2 : cap == 96 ? 3 : cap == 128 ? 4 : cap == -1 ? 5 : -1;
+  if (ka < 0 || ka >= HF_NUM_KINDS || kb < -1 || kb >= HF_NUM_KINDS || b < 0 || c < 0) return -1;
+  return ((ka * (HF_NUM_KINDS + 1) + kb + 1) * 3 + b) * 6 + c;
+}
+
+// Called for every launch: one table access (the search through the registry's
+// 837 entries took longer than the rest of the call's checks together).
 const KernelEntry* find_kernel(int ka, int kb, int block, int cap) {
-  for (const KernelEntry& e : registry())
-    if (e.kind_a == ka && e.kind_b == kb && e.block == block && e.cap == cap) return &e;
-  return nullptr;
+  static const std::vector<const KernelEntry*> table = [] {
+    std::vector<const KernelEntry*> t(HF_NUM_KINDS * (HF_NUM_KINDS + 1) * 3 * 6, nullptr);
+    for (const KernelEntry& e : registry()) {
+      const int i = entry_index(e.kind_a, e.kind_b, e.block, e.cap);
+      if (i >= 0 && !t[i]) t[i] = &e;
+    }
+    return t;
+  }();
+  const int i = entry_index(ka, kb, block, cap);
+  return i < 0 ? nullptr : table[i];
 }
 
 bool cap_in_menu(int cap) {
@@ -487,9 +504,18 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int resident
 
 int occupancy_grid(DeviceState* s, const void* fn, int block, int* wg_per_cu) {
   int occ = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, block, 0);
-  if (e != hipSuccess) return record_hip(e);
-  if (occ < 1) occ = 1;
+  {
+    std::lock_guard<std::mutex> lk(s->occ_mu);
+    const auto it = s->occ.find(fn);
+    if (it != s->occ.end()) occ = it->second;
+  }
+  if (occ == 0) {
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, block, 0);
+    if (e != hipSuccess) return record_hip(e);
+    if (occ < 1) occ = 1;
+    std::lock_guard<std::mutex> lk(s->occ_mu);
+    s->occ[fn] = occ;
+  }
   if (wg_per_cu) *wg_per_cu = occ;
   return occ * s->num_cus;
 }
@@ -514,6 +540,8 @@ int wait_event(hipEvent_t ev) {
   const long limit = env ? std::atol(env) : 0;
   if (limit <= 0) {
     hipError_t e = hipEventSynchronize(ev);
+// Resident workgroups of a kernel on the device; asked of the runtime once per
+// kernel and device (a property of the two, 1-2 us a time).
     return e == hipSuccess ? HF_OK : record_hip(e);
   }
   const auto t0 = std::chrono::steady_clock::now();

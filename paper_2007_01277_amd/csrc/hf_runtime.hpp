@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <mutex>
+#include <unordered_map>
 #include <vector>
 
 #include "../../include/hfuse.h"
@@ -24,6 +26,8 @@ struct DeviceState {
   void* scrub = nullptr;                             // 1 GiB cache scrub buffer
   void* warm = nullptr;                              // sink of the warm-up kernel
   void* static_scratch = nullptr;                    // device address of the static scratch array
+  std::mutex occ_mu;
+  std::unordered_map<const void*, int> occ;          // resident workgroups per CU of each kernel asked for
 };
 
 // Solo launches a featurisation made and their summed time (the learned
