@@ -395,7 +395,14 @@ struct Sha512 {
 // walks whose row reads are issued back to back, so every wavefront keeps
 // 8 * kChains reads in flight per step.  Lanes past the last instance redo
 // the last instance and store nothing, so every lane takes part in every
-// permute.
+// permute.  A walk is 64 dependent row reads, so two passes in a row cost twice
+// the latency of one: while there are wavefronts for it (n <= 32 per wavefront of
+// the launch) each takes 32 instances and one pass, and they are spread over the
+// workgroups, which brings the misses of one CU down and the CUs in use up.  Alone
+// at block 256, 512 and 1024, 64 packed and 32 spread: 16000 walks 95, 106, 162 and
+// 51 us; 40000 walks 111, 121, 185 and 76; 81000 walks 143, 145, 200 and 115.
+// Beyond, where HBM is busy with any split, 64 and packed (102013 walks next to a
+// histogram: 151 us spread, 144 packed).
 struct EthashLike {
   // 78 VGPRs alone; next to some bodies the compiler takes 104 and four waves per
   // SIMD (with sha256d, split 6 of 8, block 512: 708 us; at six waves 559)
@@ -411,6 +418,14 @@ struct EthashLike {
   // the big-endian 64-bit message word k of the header (bytes 8k .. 8k+7)
   __device__ static __forceinline__ uint64_t hdr64(const uint32_t* hdr, int k) {
     return ((uint64_t)__builtin_bswap32(hdr[2 * k]) << 32) | __builtin_bswap32(hdr[2 * k + 1]);
+  }
+
+  // Index of the calling wavefront in the launch for walks that may not fill it:
+  // one wavefront of every workgroup before a second of any, so that they reach as
+  // many CUs as there are workgroups, and not the same wavefront of each, which
+  // would be the same SIMD.
+  __device__ static __forceinline__ uint32_t spread_wave(const Part& p) {
+    return (p.wave + p.wg) % p.nwaves * p.nwg + p.wg;
   }
 
   template <class Bar>
@@ -431,8 +446,10 @@ struct EthashLike {
     const uint32_t lane = lane_id();
     const uint32_t grp = lane >> 3, gl = lane & 7u, q = gl & 3u;
     const uint32_t gbase = lane & ~7u;
-    const uint32_t stride = kPerIter * p.nwg * p.nwaves;
-    for (uint32_t base = kPerIter * (p.wg * p.nwaves + p.wave); base < a.n; base += stride) {  // wave-uniform
+    const uint32_t nw = p.nwg * p.nwaves;
+    const bool one = (a.n + kPerPass - 1u) / kPerPass <= nw;  // one pass each
+    const uint32_t per = one ? kPerPass : kPerIter;           // instances per iteration
+    for (uint32_t base = per * (one ? spread_wave(p) : p.wg * p.nwaves + p.wave); base < a.n; base += per * nw) {  // wave-uniform
       // this lane's seed: SHA-512 of instance base + lane, as 16 little-endian words
       uint32_t sd[16];
       {
@@ -459,7 +476,7 @@ struct EthashLike {
         }
       }
 #pragma unroll 1
-      for (uint32_t pass = 0; pass < kPerIter / kPerPass; ++pass) {
+      for (uint32_t pass = 0; pass < per / kPerPass; ++pass) {
         const uint32_t pbase = base + kPerPass * pass;
         if (pbase >= a.n) break;  // wave-uniform
         // walk h of group grp is instance pbase + 8h + grp, whose seed lane

@@ -466,6 +466,12 @@ int prepare(const hf_task* t, void* scratch, bool own, DevTask* dt) {
   return HF_EINVAL;
 }
 
+// Units of maxpool's general path (128 outputs each) that a wavefront takes once
+// the resident workgroups are busy: one is too little to pay for a workgroup more
+// (3x3 / stride 1 over [26,256,56,56], next to a table walk: 120 us with one, 96
+// with four; 2x2 over [29,32,56,56] fits the chip: 12 us with one, 15 with four).
+constexpr int64_t kPoolUnits = 4;
+
 // Workgroups that still find work when the task runs on `waves` wavefronts per
 // workgroup (1 for an empty task).
 int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves) {
@@ -480,7 +486,7 @@ int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves) {
     case HF_MAXPOOL: units = cdiv(d.pool.row3 ? d.pool.row_units : d.pool.units, waves); break;
     case HF_SHA256D:
     case HF_BLAKE2B: units = cdiv(d.sha.n, 64 * waves); break;
-    case HF_ETHASH: units = cdiv(d.eth.n, EthashLike::kPerIter * waves); break;
+    case HF_ETHASH: units = cdiv(d.eth.n, EthashLike::kPerPass * waves); break;
   }
   return std::max<int64_t>(units, 1);
 }
@@ -495,13 +501,26 @@ int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves) {
 // writes, is no faster that way (97 us resident, 102 in order with its three
 // units per wavefront, 118 with one).  The other kinds keep state per workgroup
 // or per range of work (histogram bins and their merge, channel partials,
-// hoisted hash rounds).
-uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int resident) {
-  const int64_t need = useful_wgs(t, d, waves);
-  const bool stream = t->kind == HF_UPSAMPLE || t->kind == HF_MAXPOOL;
+// hoisted hash rounds).  Where only one workgroup fits a CU (block 1024 with more
+// than 64 VGPRs), the gaps between workgroups are not covered by others, and the
+// streaming kinds run resident too (maxpool next to a histogram at 12 of 16: 46
+// us in order, 36 resident).
+uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int resident, int num_cus) {
+  int64_t need = useful_wgs(t, d, waves);
+  if (t->kind == HF_MAXPOOL && !d.pool.row3)
+    need = std::max(std::min<int64_t>(need, resident), (need + kPoolUnits - 1) / kPoolUnits);
+  if (t->kind == HF_ETHASH) {
+    if (need > resident)  // two passes per wavefront, packed
+      need = (need + 1) / 2;
+    else  // one pass, to one wavefront of every workgroup first
+      need = ((int64_t)d.eth.n + EthashLike::kPerPass - 1) / EthashLike::kPerPass;
+  }
+  const bool stream = (t->kind == HF_UPSAMPLE || t->kind == HF_MAXPOOL) && resident >= 2 * num_cus;
   return (uint32_t)(stream ? std::min<int64_t>(need, INT32_MAX) : std::min<int64_t>(need, resident));
 }
 
+// Resident workgroups of a kernel on the device; asked of the runtime once per
+// kernel and device (a property of the two, 1-2 us a time).
 int occupancy_grid(DeviceState* s, const void* fn, int block, int* wg_per_cu) {
   int occ = 0;
   {
@@ -540,8 +559,6 @@ int wait_event(hipEvent_t ev) {
   const long limit = env ? std::atol(env) : 0;
   if (limit <= 0) {
     hipError_t e = hipEventSynchronize(ev);
-// Resident workgroups of a kernel on the device; asked of the runtime once per
-// kernel and device (a property of the two, 1-2 us a time).
     return e == hipSuccess ? HF_OK : record_hip(e);
   }
   const auto t0 = std::chrono::steady_clock::now();
@@ -583,7 +600,7 @@ int launch_solo(DeviceState* s, const hf_task* t, int block, int grid, int slot,
   if (grid <= 0) {
     const int g = occupancy_grid(s, k->fn, block, nullptr);
     if (g < 0) return g;
-    grid = (int)default_wgs(t, d, block / 64, g);
+    grid = (int)default_wgs(t, d, block / 64, g, s->num_cus);
   }
   void* args[] = {&d};
   hipError_t e = hipLaunchKernel(k->fn, dim3(grid), dim3(block), args, 0, st);
@@ -633,8 +650,8 @@ int launch_fused(DeviceState* s, const hf_pair* pr, const hf_config* cfg, hipStr
   if (cfg->grid <= 0) {
     const int g = occupancy_grid(s, k->fn, cfg->block, nullptr);
     if (g < 0) return g;
-    g1 = default_wgs(ta, da, w1, g);
-    g2 = default_wgs(tb, db, W - w1, g);
+    g1 = default_wgs(ta, da, w1, g, s->num_cus);
+    g2 = default_wgs(tb, db, W - w1, g, s->num_cus);
   }
   const int grid = (int)std::max(g1, g2);
   if (grid_used) *grid_used = grid;

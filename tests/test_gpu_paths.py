@@ -152,3 +152,19 @@ def test_maxpool_without_padding(k, s, shape, special):
         c = G.pool_case(shape, k, s, 0, offset=off, x=x)
         for block in (256, 1024):
             G.run_and_check(lambda: H.hf_run_solo(c.task, block), [c])
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 127, 129, 300, 1025])
+def test_ethash_one_and_two_passes_per_wavefront(n):
+    c = G.hash_case(H.HF_ETHASH, n, seed=n)
+    for block, grid in ((256, 1), (256, 2), (512, 0), (1024, 1), (1024, 0)):
+        G.run_and_check(lambda: H.hf_run_solo(c.task, block, grid), [c])
+
+
+@pytest.mark.parametrize("n,c,h", [(1, 3, 20), (2, 64, 57), (12, 64, 113)])
+def test_maxpool_general_path_units_per_wavefront(n, c, h):
+    """Fewer units than wavefronts on the chip, some more, and several each."""
+    x = (n, c, h, h)
+    cs = G.pool_case(x, (3, 3), 1, 1, seed=h)
+    for block in (256, 1024):
+        G.run_and_check(lambda: H.hf_run_solo(cs.task, block, 0), [cs])
