@@ -326,10 +326,11 @@ static int batch_create(const hf_task* tasks, int ntask, const int32_t* group_of
   int rc;
   // groups: consecutive runs of equal ids, ids nondecreasing, 1..4 members
   std::vector<int32_t> first{0};
-  bool any_hist = false;
+  bool any_hist = false, hash = false;
   for (int i = 0; i < ntask; ++i) {
     if ((rc = validate_task(&tasks[i])) != HF_OK) return rc;
     any_hist = any_hist || tasks[i].kind == HF_LDS_HIST;
+    hash = hash || is_hash_kind(tasks[i].kind);
     if (i > 0 && group_of_task[i] != group_of_task[i - 1]) {
       if (group_of_task[i] < group_of_task[i - 1]) return HF_EINVAL;
       first.push_back(i);
@@ -378,6 +379,7 @@ static int batch_create(const hf_task* tasks, int ntask, const int32_t* group_of
   B->ntask = ntask;
   B->ngroup = ngroup;
   B->interval_waves = iw;
+  B->hash = hash;
   B->tasks.assign(tasks, tasks + ntask);
   // scratch: one 256-byte aligned region per task that needs it
   std::vector<size_t> soff(ntask, 0);
@@ -401,10 +403,35 @@ static int batch_create(const hf_task* tasks, int ntask, const int32_t* group_of
       return record_hip(e);
     }
   }
+  // the resident workgroups
+  B->lds_bytes = lds_bytes;
+  const void* fn = iw > 0 ? batch_dyn_kernel(block, hash) : batch_kernel(block, hash);
+  int occ = 0;
+  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, block, B->lds_bytes)) != hipSuccess) {
+    batch_free(B);
+    return record_hip(e);
+  }
+  if (occ < 1) {
+    batch_free(B);
+    return HF_EUNSUPPORTED;
+  }
+  const int64_t per_wg = iw > 0 ? W / iw : 1;  // workers per workgroup
   // device task arguments; virtual workgroups: enough for every member's
   // units, but items of about item_bytes of traffic, so that the per-item
-  // synchronisation stays cheap
-  const double item_bytes = 1024.0 * (sc.item_kb > 0 ? sc.item_kb : 256);
+  // synchronisation stays cheap.  A batch too small to give every resident
+  // worker two such items is cut finer, down to 16 KiB per wavefront of a static
+  // item (whose members share its wavefronts) and 32 KiB per wavefront of a
+  // worker: below that the cross-item merges and the pulls cost more than the
+  // idle workers (40 instances of 2^8 .. 2^14 elements, static: 18 items 88 us,
+  // 63 items 49, 126 items 50; 40 of 2^12 .. 2^18, one-wavefront workers: 266
+  // items 116, 2051 items 91, 4069 items 108; 734 of 2^10 .. 2^13: 106, 110, 126).
+  constexpr double kItemsPerWorker = 2.0;
+  const double kMinItemBytes = iw > 0 ? 32768.0 * iw : 16384.0 * W;
+  double all_bytes = 0.0;
+  for (int i = 0; i < ntask; ++i) all_bytes += est_cost_us(&tasks[i]) * 5.0e6;
+  const double fill = all_bytes / (kItemsPerWorker * (double)occ * s->num_cus * (double)per_wg);
+  const double item_bytes =
+      std::min(1024.0 * (sc.item_kb > 0 ? sc.item_kb : 256), std::max(fill, kMinItemBytes));
   std::vector<DevTask> dts(ntask);
   std::vector<int32_t> kinds(ntask);
   for (int i = 0; i < ntask; ++i) {
@@ -415,7 +442,6 @@ static int batch_create(const hf_task* tasks, int ntask, const int32_t* group_of
       return rc;
     }
     kinds[i] = tasks[i].kind;
-    B->hash = B->hash || is_hash_kind(tasks[i].kind);
   }
   auto al = [](size_t v) { return (v + 255) & ~size_t(255); };
   std::vector<char> host;
@@ -520,18 +546,6 @@ static int batch_create(const hf_task* tasks, int ntask, const int32_t* group_of
     batch_free(B);
     return record_hip(e);
   }
-  B->lds_bytes = lds_bytes;
-  const void* fn = iw > 0 ? batch_dyn_kernel(block, B->hash) : batch_kernel(block, B->hash);
-  int occ = 0;
-  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, block, B->lds_bytes)) != hipSuccess) {
-    batch_free(B);
-    return record_hip(e);
-  }
-  if (occ < 1) {
-    batch_free(B);
-    return HF_EUNSUPPORTED;
-  }
-  const int64_t per_wg = iw > 0 ? W / iw : 1;  // workers per workgroup
   const int64_t want = ((int64_t)B->total_items + per_wg - 1) / per_wg;
   B->grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)occ * s->num_cus, want));
   *out = B;
