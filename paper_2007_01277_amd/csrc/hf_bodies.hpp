@@ -23,12 +23,13 @@ struct BnArgs {  // per-channel mean / biased variance of NCHW fp32
   const float* x;
   float* mean;
   float* var;
-  uint32_t* ctr;   // [C] unit arrival counters (zero between launches)
+  uint32_t* ctr;   // [C << ctr_shift] unit arrival counters (zero between launches)
   uint32_t* part;  // [C][upc][2] per-unit (mean, M2) as float bits
   uint32_t C, HW, M, CHWm;  // M = N*HW elements per channel, CHWm = (C-1)*HW
   uint32_t upc;             // units per channel
   uint32_t total;           // C * upc
   uint32_t vec;             // float4 path: HW % 4 == 0 and x 16-byte aligned
+  uint32_t ctr_shift;       // the counters lie 1 << ctr_shift words apart
   FastDiv div_hw, div_upc;
 };
 
@@ -176,6 +177,20 @@ __device__ __forceinline__ uint32_t arrive_after_coherent_stores(uint32_t* ctr, 
 //   Chan's pairwise update, and writes mean[c] and var[c] = M2 / M.
 // The unit results and their merge order do not depend on which wavefront
 // computed a unit, so every grid and split gives the same bits.
+//
+// What bounds it besides the reads: the arrivals.  Atomics on one line are served
+// one after the other, some 13 ns each, so the counters of few channels lie in
+// lines of their own where the scratch has room (own_ctr_shift): [76,16,56,56] 49
+// us in one line, 10 in sixteen; [54,32,56,112] 51 and 15; [64,256,56,56] 45 and 44.
+// The merge asks for four of a lane's unit results at a time.
+//
+// Short channels are handed out whole: the wavefront keeps the unit results in its
+// lanes, as the merge would read them back, and merges at once, so nothing is
+// published, counted, waited for or zeroed (each a trip to memory, one after the
+// other).  [128,1024,7,7] alone, at block 256, 512 and 1024: 13, 14 and 12 us with
+// every unit published, 9.8, 9.3 and 9.2 whole; [32,512,14,14] (seven units): 9.3
+// and 7.6.  Fewer or longer channels than that would leave CUs idle ([1,64,56,112],
+// seven units: 7.5 us cut, 12 whole).
 struct BnStats {
 #ifndef HF_BN_VEC
 #define HF_BN_VEC 4
@@ -187,6 +202,11 @@ struct BnStats {
   static constexpr uint32_t kVals = 4 * kVec;      // values per lane per unit
   static constexpr uint32_t kUnit = 64 * kVals;    // 1024 elements by default
   static constexpr uint32_t kDepth = HF_BN_DEPTH;  // units in flight per wavefront
+  // Channels short enough to be handed out whole (below): a unit or two always,
+  // up to eight units where there is a channel for every CU.
+  __host__ __device__ static constexpr bool whole_channels(uint32_t upc, uint32_t C) {
+    return upc <= 2u || (upc <= 8u && C >= 256u);
+  }
   static constexpr uint32_t lds_words(int) { return 0; }
 
   struct Regs {
@@ -310,7 +330,7 @@ struct BnStats {
       const uint32_t n = min(uend - u, a.upc - k0);
       segment<VEC>(a, c, k0, u, n, lane);
       uint32_t old = 0;
-      if (lane == 0) old = arrive_after_coherent_stores(a.ctr + c, n);
+      if (lane == 0) old = arrive_after_coherent_stores(a.ctr + ((size_t)c << a.ctr_shift), n);
       old = uniform(old);
       if (old + n == a.upc) finish_channel(a, c, lane);
       u += n;
@@ -323,6 +343,19 @@ struct BnStats {
     const uint32_t lane = lane_id();
     const uint32_t nw = p.nwg * p.nwaves;
     const uint32_t gw = p.wg * p.nwaves + p.wave;
+    if (whole_channels(a.upc, a.C)) {
+      // a balanced range of neighbours for each workgroup (their planes share
+      // lines), from a different wavefront, which is another SIMD, in each
+      const uint32_t q = a.C / p.nwg, r = a.C - q * p.nwg;
+      const uint32_t cbeg = p.wg * q + min(p.wg, r);
+      const uint32_t cend = cbeg + q + (p.wg < r ? 1u : 0u);
+      const uint32_t first = cbeg + (p.wave + p.wg) % p.nwaves;
+      if (a.vec)
+        for (uint32_t c = first; c < cend; c += p.nwaves) whole<true>(a, c, lane);
+      else
+        for (uint32_t c = first; c < cend; c += p.nwaves) whole<false>(a, c, lane);
+      return;
+    }
     const uint32_t q = a.total / nw, r = a.total - q * nw;
     const uint32_t ubeg = gw * q + min(gw, r);
     const uint32_t uend = ubeg + q + (gw < r ? 1u : 0u);
@@ -331,6 +364,36 @@ struct BnStats {
       run_range<true>(a, ubeg, uend, lane);
     else
       run_range<false>(a, ubeg, uend, lane);
+  }
+
+  // Channel c, all of whose units (at most 64) this wavefront reduces: unit k's
+  // (mean, M2) stays in lane k, where the merge wants it.
+  template <bool VEC>
+  __device__ static __forceinline__ void whole(const BnArgs& a, uint32_t c, uint32_t lane) {
+    // offsets and counts are the same for every channel: kept from the compiler,
+    // which would hold the addresses of 16 loads and every division of the merge
+    // in registers across the channels (126 VGPRs)
+    asm volatile("" : "+v"(lane));
+    float mu_k = 0.f, m2_k = 0.f;
+    Regs cur, nxt;
+    load_unit<VEC>(a, c, 0u, lane, cur);
+#pragma unroll 1
+    for (uint32_t k = 0; k < a.upc; ++k) {
+      // the last unit again past the end, so that the loop has no branch
+      load_unit<VEC>(a, c, min(k + 1u, a.upc - 1u) * kUnit, lane, nxt);
+      float mu, m2;
+      unit_stats<VEC, false>(a, cur, k * kUnit, lane, mu, m2);
+      mu_k = lane == k ? mu : mu_k;
+      m2_k = lane == k ? m2 : m2_k;
+      cur = nxt;
+    }
+    double n = 0.0, m = 0.0, m2 = 0.0;
+    if (lane < a.upc) chan(n, m, m2, (double)min(kUnit, a.M - lane * kUnit), (double)mu_k, (double)m2_k);
+    if (a.upc > 1u) butterfly(lane, n, m, m2);  // one unit: itself
+    if (lane == 0) {
+      a.mean[c] = (float)m;
+      a.var[c] = (float)(m2 / (double)a.M);
+    }
   }
 
   // Chan et al. pairwise update of (n, mean, M2) with (nb, mb, m2b), in double.
@@ -343,17 +406,8 @@ struct BnStats {
     n = nab;
   }
 
-  // Merge the units of channel c: each lane merges units lane, lane+64, ... in
-  // order, then the 64 lane results are merged by a fixed butterfly.
-  __device__ static __forceinline__ void finish_channel(const BnArgs& a, uint32_t c, uint32_t lane) {
-    const uint32_t base = 2u * c * a.upc;
-    double n = 0.0, m = 0.0, m2 = 0.0;
-    for (uint32_t k = lane; k < a.upc; k += 64u) {
-      const double nk = (double)min(kUnit, a.M - k * kUnit);
-      const double mk = (double)__builtin_bit_cast(float, load_agent(a.part + base + 2u * k));
-      const double m2k = (double)__builtin_bit_cast(float, load_agent(a.part + base + 2u * k + 1u));
-      chan(n, m, m2, nk, mk, m2k);
-    }
+  // The 64 lanes' (n, m, m2) merged, the same in every lane.
+  __device__ static __forceinline__ void butterfly(uint32_t lane, double& n, double& m, double& m2) {
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const double nb = __shfl_xor(n, off, kWave);
@@ -378,15 +432,36 @@ struct BnStats {
         }
       }
     }
-    // leave the scratch zero-filled, as every kernel of the library does
-    for (uint32_t k = lane; k < a.upc; k += 64u) {
-      store_agent(a.part + base + 2u * k, 0u);
-      store_agent(a.part + base + 2u * k + 1u, 0u);
+  }
+
+  // Merge the units of channel c: each lane merges units lane, lane+64, ... in
+  // order, then the 64 lane results are merged by a fixed butterfly.
+  __device__ static __forceinline__ void finish_channel(const BnArgs& a, uint32_t c, uint32_t lane) {
+    uint64_t* part = reinterpret_cast<uint64_t*>(a.part) + (size_t)c * a.upc;
+    double n = 0.0, m = 0.0, m2 = 0.0;
+    constexpr uint32_t kReads = 4;  // of a lane's units, requested together
+#pragma unroll 1
+    for (uint32_t k0 = lane; k0 < a.upc; k0 += 64u * kReads) {
+      uint64_t v[kReads];
+#pragma unroll
+      for (uint32_t t = 0; t < kReads; ++t)
+        v[t] = __hip_atomic_load(part + min(k0 + 64u * t, a.upc - 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (uint32_t t = 0; t < kReads; ++t) {
+        const uint32_t k = k0 + 64u * t;
+        if (k < a.upc)
+          chan(n, m, m2, (double)min(kUnit, a.M - k * kUnit), (double)__builtin_bit_cast(float, (uint32_t)v[t]),
+               (double)__builtin_bit_cast(float, (uint32_t)(v[t] >> 32)));
+      }
     }
+    butterfly(lane, n, m, m2);
+    // leave the scratch zero-filled, as every kernel of the library does
+    for (uint32_t k = lane; k < a.upc; k += 64u)
+      __hip_atomic_store(part + k, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (lane == 0) {
       a.mean[c] = (float)m;
       a.var[c] = (float)(m2 / (double)a.M);
-      store_agent(a.ctr + c, 0u);  // leave the counter zero for the next launch
+      store_agent(a.ctr + ((size_t)c << a.ctr_shift), 0u);  // leave the counter zero for the next launch
     }
   }
 };

@@ -293,9 +293,17 @@ int64_t scratch_bytes(const hf_task* t) {
   }
 }
 
+// Statistics in the library's own scratch: log2 of the words from one arrival
+// counter to the next.  A 128-byte line for each of up to 2048 channels (256 KiB;
+// [76,16,56,56], whose 3728 arrivals otherwise queue on one line: 49 us packed, 10
+// in lines); more channels than that have arrivals on 64 lines and more as they are.
+static uint32_t own_ctr_shift(const hf_task* t) { return t->c <= 2048 ? 5u : 0u; }
+
 // Scratch of a task in the library's own memory: a histogram there gets all
-// its accumulators.
+// its accumulators, statistics counters in lines of their own.
 size_t own_scratch_bytes(const hf_task* t) {
+  if (t->kind == HF_BN_STATS && scratch_bytes(t) > 0)
+    return (size_t)scratch_bytes(t) + 4 * ((size_t)t->c << own_ctr_shift(t));
   if (t->kind == HF_LDS_HIST) return 4 * (256 * (size_t)LdsHist::kSums + 32 * (1 + (size_t)LdsHist::kSums));
   return (size_t)std::max<int64_t>(scratch_bytes(t), 0);
 }
@@ -310,7 +318,8 @@ int prepare(const hf_task* t, void* scratch, bool own, DevTask* dt) {
       a.x = static_cast<const float*>(t->in);
       a.mean = static_cast<float*>(t->out0);
       a.var = static_cast<float*>(t->out1);
-      const uint32_t ctrw = (uint32_t)((t->c + 63) / 64 * 64);
+      a.ctr_shift = own ? own_ctr_shift(t) : 0u;
+      const uint32_t ctrw = (uint32_t)(((t->c << a.ctr_shift) + 63) / 64 * 64);
       a.ctr = static_cast<uint32_t*>(scratch);
       a.part = static_cast<uint32_t*>(scratch) + ctrw;
       a.C = (uint32_t)t->c;
@@ -478,7 +487,7 @@ int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves) {
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   int64_t units = 1;
   switch (t->kind) {
-    case HF_BN_STATS: units = cdiv(d.bn.total, waves); break;
+    case HF_BN_STATS: units = cdiv(BnStats::whole_channels(d.bn.upc, d.bn.C) ? d.bn.C : d.bn.total, waves); break;
     case HF_INT_MIX: units = cdiv(d.mix.n4 ? d.mix.n4 : d.mix.n, 64 * waves); break;
     case HF_LDS_HIST: units = cdiv(std::max<uint32_t>(d.hist.n16, 1), 64 * waves); break;
     case HF_IM2COL: units = cdiv(d.im2col.row3 ? d.im2col.row_units : cdiv(d.im2col.items, 64), waves); break;
@@ -509,6 +518,9 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int resident
   int64_t need = useful_wgs(t, d, waves);
   if (t->kind == HF_MAXPOOL && !d.pool.row3)
     need = std::max(std::min<int64_t>(need, resident), (need + kPoolUnits - 1) / kPoolUnits);
+  // whole channels: a workgroup for every CU before a second wavefront of any
+  if (t->kind == HF_BN_STATS && BnStats::whole_channels(d.bn.upc, d.bn.C))
+    need = std::max(need, std::min<int64_t>(d.bn.C, num_cus));
   if (t->kind == HF_ETHASH) {
     if (need > resident)  // two passes per wavefront, packed
       need = (need + 1) / 2;

@@ -154,6 +154,46 @@ def test_maxpool_without_padding(k, s, shape, special):
             G.run_and_check(lambda: H.hf_run_solo(c.task, block), [c])
 
 
+@pytest.mark.parametrize("hw", [1, 255, 256, 257, 512, 513, 700, 2048, 2049])
+def test_bn_whole_channels_equal_cut_ones(hw):
+    """256 channels of up to eight units (1024 elements each) are handed out whole,
+    16 channels of more than two are cut: the same bits, at every grid."""
+    x = G.dev(inputs.bn_input((4, 256, 1, hw), hw))
+
+    def stats(xs, block, grid):
+        o = [_out((xs.shape[1],), 0) for _ in range(2)]
+        return _run((H.task_bn_stats(xs, *o), o), block, grid)
+
+    parts = [stats(x[:, c:c + 16].contiguous(), 256, 0) for c in range(0, 256, 16)]
+    want = [torch.cat(p) for p in zip(*parts)]
+    for block, grid in ((256, 0), (512, 0), (1024, 0), (256, 1), (256, 3), (1024, 300)):
+        got = stats(x, block, grid)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (block, grid)
+
+
+@pytest.mark.parametrize("shape", [(2, 1, 300, 301), (3, 16, 64, 64), (1, 2048, 97, 96), (1, 2049, 96, 97)])
+def test_bn_counters_in_lines_and_packed(shape):
+    """A line for each counter (the library's scratch, up to 2048 channels) and
+    packed counters (the caller's) count the same arrivals and end at zero."""
+    x = inputs.cuda_normal(shape, sum(shape))
+    res = []
+    for own in (True, False):
+        o = [_out((shape[1],), 0) for _ in range(2)]
+        t = H.task_bn_stats(x, *o)
+        if not own:
+            scr = torch.zeros(H.hf_scratch_bytes(t) // 4, dtype=torch.int32, device="cuda")
+            t.scratch = scr.data_ptr()
+        for block, grid in ((256, 0), (1024, 0), (512, 7)):  # each finds the scratch as the last left it
+            for b in o:
+                b.fill_(7)
+            _run((t, o), block, grid)
+            res.append([b.clone() for b in o])
+        if not own:
+            assert int(scr.abs().sum()) == 0
+    for r in res[1:]:
+        assert torch.equal(r[0], res[0][0]) and torch.equal(r[1], res[0][1])
+
+
 @pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 127, 129, 300, 1025])
 def test_ethash_one_and_two_passes_per_wavefront(n):
     c = G.hash_case(H.HF_ETHASH, n, seed=n)
