@@ -525,7 +525,7 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int resident
     if (need > resident)  // two passes per wavefront, packed
       need = (need + 1) / 2;
     else  // one pass, to one wavefront of every workgroup first
-      need = ((int64_t)d.eth.n + EthashLike::kPerPass - 1) / EthashLike::kPerPass;
+      need = std::max<int64_t>(1, ((int64_t)d.eth.n + EthashLike::kPerPass - 1) / EthashLike::kPerPass);
   }
   const bool stream = (t->kind == HF_UPSAMPLE || t->kind == HF_MAXPOOL) && resident >= 2 * num_cus;
   return (uint32_t)(stream ? std::min<int64_t>(need, INT32_MAX) : std::min<int64_t>(need, resident));
