@@ -44,8 +44,10 @@ struct BatchTables {
 // HASH: the variant that also runs the hash kinds.  The hash bodies need more
 // registers than the others, so batches without them use the variant that
 // leaves them out and keeps five waves per SIMD without spilling.
+// lds: the interval's histogram region, mid: its Sha256d::kMidWords words.
 template <bool HASH, class Bar>
-__device__ __forceinline__ void run_body(int kind, const DevTask& t, const Part& p, Bar& bar, uint32_t* lds) {
+__device__ __forceinline__ void run_body(int kind, const DevTask& t, const Part& p, Bar& bar, uint32_t* lds,
+                                         uint32_t* mid) {
   switch (kind) {
     case HF_BN_STATS: BnStats::run(t, p, bar, lds); break;
     case HF_INT_MIX: IntMix::run(t, p, bar, lds); break;
@@ -56,7 +58,7 @@ __device__ __forceinline__ void run_body(int kind, const DevTask& t, const Part&
     default:
       if constexpr (HASH) {
         switch (kind) {
-          case HF_SHA256D: Sha256d::run(t, p, bar, lds); break;
+          case HF_SHA256D: Sha256d::run(t, p, bar, mid); break;
           case HF_BLAKE2B: Blake2b::run(t, p, bar, lds); break;
           case HF_ETHASH: EthashLike::run(t, p, bar, lds); break;
           default: break;
@@ -76,6 +78,7 @@ template <int BLOCK, bool HASH, int WPE>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE))) k_batch(BatchTables T) {
   __shared__ uint32_t smem[kMaxMembers];
   __shared__ uint32_t item_sh[2];
+  __shared__ uint32_t mid[HASH ? kMaxMembers * Sha256d::kMidWords : 1];
   const uint32_t wave = uniform(threadIdx.x >> 6);
   if (threadIdx.x == 0)
     item_sh[0] = __hip_atomic_fetch_add(T.queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -120,7 +123,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE)
       for (int i = 0; i < (int)(sizeof(DevTask) / 4); ++i) dst[i] = uniform(src[i]);
       const int32_t slot = (int32_t)uniform((uint32_t)T.lds_slot[mine]);
       uint32_t* lds = slot >= 0 ? hf_batch_hist_lds + (uint32_t)slot * LdsHist::lds_words(BLOCK) : nullptr;
-      run_body<HASH>((int)uniform((uint32_t)T.kinds[mine]), dt, p, bar, lds);
+      run_body<HASH>((int)uniform((uint32_t)T.kinds[mine]), dt, p, bar, lds,
+                     HASH ? mid + (uint32_t)(mine - t0) * Sha256d::kMidWords : nullptr);
     }
     __syncthreads();  // item boundary: every interval has finished
   }
@@ -155,6 +159,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE)
   constexpr uint32_t W = BLOCK / 64;
   __shared__ uint32_t ctr[W];       // one interval-barrier counter per interval
   __shared__ uint32_t item_sh[W][2];
+  __shared__ uint32_t mid[HASH ? W * Sha256d::kMidWords : 1];
   const uint32_t wave = uniform(threadIdx.x >> 6);
   const uint32_t iw = T.iw;
   const uint32_t k = wave / iw, wv = wave - k * iw;
@@ -183,7 +188,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WPE)
     uint32_t* dst = reinterpret_cast<uint32_t*>(&dt);
 #pragma unroll
     for (int i = 0; i < (int)(sizeof(DevTask) / 4); ++i) dst[i] = uniform(src[i]);
-    run_body<HASH>((int)uniform((uint32_t)T.kinds[t]), dt, p, bar, lds);
+    run_body<HASH>((int)uniform((uint32_t)T.kinds[t]), dt, p, bar, lds, HASH ? mid + k * Sha256d::kMidWords : nullptr);
     bar.sync();  // every wavefront of the interval is done with this item and read the next one
   }
 }

@@ -345,11 +345,11 @@ struct BnStats {
     const uint32_t gw = p.wg * p.nwaves + p.wave;
     if (whole_channels(a.upc, a.C)) {
       // a balanced range of neighbours for each workgroup (their planes share
-      // lines), from a different wavefront, which is another SIMD, in each
+      // lines)
       const uint32_t q = a.C / p.nwg, r = a.C - q * p.nwg;
       const uint32_t cbeg = p.wg * q + min(p.wg, r);
       const uint32_t cend = cbeg + q + (p.wg < r ? 1u : 0u);
-      const uint32_t first = cbeg + (p.wave + p.wg) % p.nwaves;
+      const uint32_t first = cbeg + p.wave;
       if (a.vec)
         for (uint32_t c = first; c < cend; c += p.nwaves) whole<true>(a, c, lane);
       else
@@ -553,7 +553,7 @@ struct IntMix {
   template <class Bar>
   __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const MixArgs& a = dt.mix;
-    const uint32_t gl = p.wg * p.nlanes + p.lane;
+    const uint32_t gl = 64u * wave_index(p, ((a.n4 ? a.n4 : a.n) + 63u) / 64u) + lane_id();
     const uint32_t stride = p.nwg * p.nlanes;
     const uint32_t R = (uint32_t)a.rounds;
     const uint4* in4 = reinterpret_cast<const uint4*>(a.in);

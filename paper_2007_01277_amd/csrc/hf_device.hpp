@@ -37,6 +37,20 @@ __device__ __forceinline__ uint32_t uniform(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
+// Index of the calling wavefront in the launch: workgroup by workgroup, or (spread)
+// one wavefront of every workgroup before a second of any, so that work for less
+// than all of them reaches as many CUs as there are workgroups (the hardware starts
+// successive workgroups of a CU on successive SIMDs).
+__device__ __forceinline__ uint32_t wave_index(const Part& p, bool spread) {
+  return spread ? p.wave * p.nwg + p.wg : p.wg * p.nwaves + p.wave;
+}
+// The same for `units` pieces of which wavefront i takes i, i + all wavefronts, ...:
+// spread while nobody has a second one.  Beyond, neighbouring wavefronts keep
+// neighbouring memory (int_mix of 2^24 words, 2 rounds: 23 us, spread 25).
+__device__ __forceinline__ uint32_t wave_index(const Part& p, uint32_t units) {
+  return wave_index(p, units <= p.nwg * p.nwaves);
+}
+
 // ----------------------------------------------------------------- streaming stores
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 

@@ -66,12 +66,19 @@ __device__ __forceinline__ uint64_t shr64(uint64_t x, uint32_t n, bool uni = fal
 
 // ============================================================ SHA-256d
 // FIPS 180-4.  The first 64 header bytes are the same for every nonce, so their
-// compression (the midstate) is computed once per wavefront from uniform
-// values; each lane then compresses the second block of its message and hashes
-// the 32-byte digest again.  Bound by VALU issue: 2^22 nonces 358 us with the
-// compiler's xors, 288 us with one v_bitop3 per three-input function (op3).
+// compression (the midstate) is computed apart; each lane then compresses the
+// second block of its message and hashes the 32-byte digest again.  Bound by VALU
+// issue: 2^22 nonces 358 us with the compiler's xors, 288 us with one v_bitop3 per
+// three-input function (op3).  The midstate costs a wavefront as much as half a
+// step of 64 nonces: once there is more than one wavefront per SIMD (kAlone) the
+// interval's first wavefront computes it for all (200000 nonces at block 256, 512
+// and 1024: 33, 33 and 32 us each for itself, 25, 25 and 25 shared; 10^6: 94, 89
+// and 83, then 82, 78 and 77).  With fewer every wavefront has a SIMD of its own
+// and the hand-over would be a microsecond more (1000 nonces: 9.5 and 10.6).
 struct Sha256d {
-  static constexpr uint32_t lds_words(int) { return 0; }
+  static constexpr uint32_t kMidWords = 8;    // LDS words of an interval
+  static constexpr uint32_t kAlone = 65536u;  // nonces up to one wavefront per SIMD
+  static constexpr uint32_t lds_words(int) { return kMidWords; }
 
   // Sec. 4.2.2: round constants
   static constexpr uint32_t kK[64] = {
@@ -160,26 +167,42 @@ struct Sha256d {
     for (int k = 0; k < 8; ++k) st[k] += v[k];
   }
 
+  // lds: kMidWords of the interval, free since its last barrier
   template <class Bar>
-  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
+  __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar& bar, uint32_t* lds) {
     const ShaArgs& a = dt.sha;
     if (a.n == 0) return;
-    // midstate of the first 64 bytes (big-endian words, Sec. 5.2.1); the
-    // compiler also hoists the rounds of the second block that do not read the
+    // midstate of the first 64 bytes (big-endian words, Sec. 5.2.1)
+    const bool share = a.n > kAlone && p.nwaves > 1u;
+    const uint32_t first = 64u * wave_index(p, (a.n + 63u) / 64u);
+    if (!share && first >= a.n) return;
+    uint32_t mid[8];
+    if (!share || p.wave == 0u) {
+      uint32_t st[8], w[16];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) st[k] = kH0[k];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) w[k] = __builtin_bswap32(a.hdr[k]);
+      compress<0>(st, w);
+      // uniform across the wavefront: scalar registers, not VGPRs
+#pragma unroll
+      for (int k = 0; k < 8; ++k) mid[k] = uniform(st[k]);
+      if (share && lane_id() == 0u) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) lds[k] = mid[k];
+      }
+    }
+    if (share) {
+      bar.sync();
+#pragma unroll
+      for (int k = 0; k < 8; ++k) mid[k] = uniform(lds[k]);
+    }
+    // the compiler hoists the rounds of the second block that do not read the
     // nonce out of the loop
-    uint32_t mid[8], w[16];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) mid[k] = kH0[k];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) w[k] = __builtin_bswap32(a.hdr[k]);
-    compress<0>(mid, w);
-    // uniform across the wavefront: scalar registers, not VGPRs
-#pragma unroll
-    for (int k = 0; k < 8; ++k) mid[k] = uniform(mid[k]);
     const uint32_t t16 = __builtin_bswap32(a.hdr[16]), t17 = __builtin_bswap32(a.hdr[17]),
                    t18 = __builtin_bswap32(a.hdr[18]);
     const uint32_t stride = 64u * p.nwg * p.nwaves;
-    for (uint32_t i = 64u * (p.wg * p.nwaves + p.wave) + lane_id(); i < a.n; i += stride) {
+    for (uint32_t i = first + lane_id(); i < a.n; i += stride) {
       // second block: bytes 64..79, then the padding of an 80-byte message (Sec. 5.1.1)
       uint32_t st[8];
 #pragma unroll
@@ -251,7 +274,7 @@ struct Blake2b {
 #pragma unroll
     for (int k = 10; k < 16; ++k) m[k] = 0;
     const uint32_t stride = 64u * p.nwg * p.nwaves;
-    for (uint32_t i = 64u * (p.wg * p.nwaves + p.wave) + lane_id(); i < a.n; i += stride) {
+    for (uint32_t i = 64u * wave_index(p, (a.n + 63u) / 64u) + lane_id(); i < a.n; i += stride) {
       m[9] = m9lo | ((uint64_t)(a.nonce0 + i) << 32);
       // Sec. 3.2 with the parameter block of Sec. 2.5 (digest 32 bytes, fanout
       // and depth 1) and the byte count t = 80 of the final block
@@ -420,14 +443,6 @@ struct EthashLike {
     return ((uint64_t)__builtin_bswap32(hdr[2 * k]) << 32) | __builtin_bswap32(hdr[2 * k + 1]);
   }
 
-  // Index of the calling wavefront in the launch for walks that may not fill it:
-  // one wavefront of every workgroup before a second of any, so that they reach as
-  // many CUs as there are workgroups, and not the same wavefront of each, which
-  // would be the same SIMD.
-  __device__ static __forceinline__ uint32_t spread_wave(const Part& p) {
-    return (p.wave + p.wg) % p.nwaves * p.nwg + p.wg;
-  }
-
   template <class Bar>
   __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const EthArgs& a = dt.eth;
@@ -449,7 +464,7 @@ struct EthashLike {
     const uint32_t nw = p.nwg * p.nwaves;
     const bool one = (a.n + kPerPass - 1u) / kPerPass <= nw;  // one pass each
     const uint32_t per = one ? kPerPass : kPerIter;           // instances per iteration
-    for (uint32_t base = per * (one ? spread_wave(p) : p.wg * p.nwaves + p.wave); base < a.n; base += per * nw) {  // wave-uniform
+    for (uint32_t base = per * wave_index(p, one); base < a.n; base += per * nw) {  // wave-uniform
       // this lane's seed: SHA-512 of instance base + lane, as 16 little-endian words
       uint32_t sd[16];
       {

@@ -518,9 +518,13 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int resident
   int64_t need = useful_wgs(t, d, waves);
   if (t->kind == HF_MAXPOOL && !d.pool.row3)
     need = std::max(std::min<int64_t>(need, resident), (need + kPoolUnits - 1) / kPoolUnits);
-  // whole channels: a workgroup for every CU before a second wavefront of any
-  if (t->kind == HF_BN_STATS && BnStats::whole_channels(d.bn.upc, d.bn.C))
-    need = std::max(need, std::min<int64_t>(d.bn.C, num_cus));
+  // bodies that spread their wavefronts' work over the workgroups (wave_index, whole
+  // channels): a workgroup for every CU before a second wavefront of any (1000
+  // sha256d nonces at block 256, 512 and 1024: 9.4, 16 and 29 us packed into 4, 2
+  // and 1 workgroups, 9.5 in 16; 20000 blake2b: 7, 8 and 14, and 7)
+  const bool spread = t->kind == HF_INT_MIX || t->kind == HF_SHA256D || t->kind == HF_BLAKE2B ||
+                      (t->kind == HF_BN_STATS && BnStats::whole_channels(d.bn.upc, d.bn.C));
+  if (spread) need = std::max(need, std::min<int64_t>(useful_wgs(t, d, 1), num_cus));
   if (t->kind == HF_ETHASH) {
     if (need > resident)  // two passes per wavefront, packed
       need = (need + 1) / 2;

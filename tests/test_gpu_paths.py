@@ -208,3 +208,17 @@ def test_maxpool_general_path_units_per_wavefront(n, c, h):
     cs = G.pool_case(x, (3, 3), 1, 1, seed=h)
     for block in (256, 1024):
         G.run_and_check(lambda: H.hf_run_solo(cs.task, block, 0), [cs])
+
+
+@pytest.mark.parametrize("kind", [H.HF_SHA256D, H.HF_BLAKE2B])
+@pytest.mark.parametrize("n", [1, 65, 4097, 65536, 65537, 140_001])
+def test_hashes_spread_and_shared_midstate(kind, n):
+    """One piece per wavefront (spread over the workgroups) and several, the
+    midstate per wavefront (up to 65536 nonces) and per workgroup or interval."""
+    c = G.hash_case(kind, n, seed=n, sample=1500)
+    for block, grid in ((256, 0), (1024, 0), (512, 3), (1024, 300)):
+        G.run_and_check(lambda: H.hf_run_solo(c.task, block, grid), [c])
+    m = G.mix_case(5000, 3, seed=n)
+    for cfg in ((1, 256, 0), (12, 1024, 64)):  # an interval of one and of several wavefronts
+        for pr in (H.make_pair(c.task, m.task), H.make_pair(m.task, c.task)):
+            G.run_and_check(lambda: H.hf_run_fused_cfg(pr, H.hf_config(*cfg, 0)), [c, m])
