@@ -172,7 +172,11 @@ int arena_slot(DeviceState* s, int i, size_t bytes, void** out) {
     if (sl.ptr) (void)hipFree(sl.ptr);
     sl.ptr = nullptr;
     sl.bytes = 0;
-    const size_t want = std::max<size_t>((bytes + (1u << 20) - 1) & ~size_t((1u << 20) - 1), 1u << 20);
+    // with room for what own_scratch_bytes adds to scratch_bytes (at most 256 KiB and
+    // 18 KiB), so that a task whose scratch_bytes fits a slot's whole MiB never grows
+    // it: growing is not possible while a stream is captured
+    const size_t want =
+        std::max<size_t>((bytes + (1u << 20) - 1) & ~size_t((1u << 20) - 1), 1u << 20) + (512u << 10);
     if ((e = hipMalloc(&sl.ptr, want)) != hipSuccess) {
       record_hip(e);
       return HF_ENOMEM;
