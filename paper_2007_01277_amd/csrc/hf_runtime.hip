@@ -504,8 +504,8 @@ int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves) {
   return std::max<int64_t>(units, 1);
 }
 
-// Workgroups a task runs on by default, `waves` wavefronts of each, where
-// `resident` workgroups fit the chip at once.  Upsample and maxpool stream
+// Workgroups a task runs on by default, `waves` wavefronts of each of `block`
+// lanes, where `resident` workgroups fit the chip at once.  Upsample and maxpool stream
 // through HBM and get a workgroup for every unit of work, however many that is:
 // workgroups start in order, so those in flight always work on one narrow window
 // of the tensors, where resident wavefronts that stride through them drift apart
@@ -518,7 +518,7 @@ int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves) {
 // than 64 VGPRs), the gaps between workgroups are not covered by others, and the
 // streaming kinds run resident too (maxpool next to a histogram at 12 of 16: 46
 // us in order, 36 resident).
-uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int resident, int num_cus) {
+uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int block, int resident, int num_cus) {
   int64_t need = useful_wgs(t, d, waves);
   if (t->kind == HF_MAXPOOL && !d.pool.row3)
     need = std::max(std::min<int64_t>(need, resident), (need + kPoolUnits - 1) / kPoolUnits);
@@ -536,7 +536,9 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int resident
       need = std::max<int64_t>(1, ((int64_t)d.eth.n + EthashLike::kPerPass - 1) / EthashLike::kPerPass);
   }
   const bool stream = (t->kind == HF_UPSAMPLE || t->kind == HF_MAXPOOL) && resident >= 2 * num_cus;
-  return (uint32_t)(stream ? std::min<int64_t>(need, INT32_MAX) : std::min<int64_t>(need, resident));
+  // a launch has fewer than 2^32 lanes; the bodies are grid-stride loops
+  const int64_t most = stream ? (int64_t)(UINT32_MAX / (uint32_t)block) : resident;
+  return (uint32_t)std::min<int64_t>(need, most);
 }
 
 // Resident workgroups of a kernel on the device; asked of the runtime once per
@@ -620,7 +622,7 @@ int launch_solo(DeviceState* s, const hf_task* t, int block, int grid, int slot,
   if (grid <= 0) {
     const int g = occupancy_grid(s, k->fn, block, nullptr);
     if (g < 0) return g;
-    grid = (int)default_wgs(t, d, block / 64, g, s->num_cus);
+    grid = (int)default_wgs(t, d, block / 64, block, g, s->num_cus);
   }
   void* args[] = {&d};
   hipError_t e = hipLaunchKernel(k->fn, dim3(grid), dim3(block), args, 0, st);
@@ -670,8 +672,8 @@ int launch_fused(DeviceState* s, const hf_pair* pr, const hf_config* cfg, hipStr
   if (cfg->grid <= 0) {
     const int g = occupancy_grid(s, k->fn, cfg->block, nullptr);
     if (g < 0) return g;
-    g1 = default_wgs(ta, da, w1, g, s->num_cus);
-    g2 = default_wgs(tb, db, W - w1, g, s->num_cus);
+    g1 = default_wgs(ta, da, w1, cfg->block, g, s->num_cus);
+    g2 = default_wgs(tb, db, W - w1, cfg->block, g, s->num_cus);
   }
   const int grid = (int)std::max(g1, g2);
   if (grid_used) *grid_used = grid;

@@ -58,6 +58,7 @@ int wait_event(hipEvent_t ev);
 int kernel_info(DeviceState* s, const void* fn, int block, hf_kernel_info* out);
 void mlp_free();
 int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves);
+uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int block, int resident, int num_cus);
 int occupancy_grid(DeviceState* s, const void* fn, int block, int* wg_per_cu);
 
 }  // namespace hf

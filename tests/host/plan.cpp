@@ -1,0 +1,28 @@
+// The launch decisions of the library's host code as plain C functions, for the
+// tests of those decisions.  Host code only: no HIP call is made and no pointer of
+// a task is followed.
+#include "../../paper_2007_01277_amd/csrc/hf_runtime.hpp"
+
+static hf::DevTask prepared(const hf_task* t, bool own) {
+  hf::DevTask d;
+  if (hf::prepare(t, nullptr, own, &d) != HF_OK) std::abort();
+  return d;
+}
+
+extern "C" {
+
+// Workgroups of `block` lanes by default for a task that has `waves` wavefronts of
+// each, where `resident` of them fit the chip's `num_cus` compute units.  own: its
+// scratch is the library's.
+uint32_t plan_wgs(const hf_task* t, int own, int waves, int block, int resident, int num_cus) {
+  const hf::DevTask d = prepared(t, own != 0);
+  return hf::default_wgs(t, d, waves, block, resident, num_cus);
+}
+
+// Workgroups that find work.
+int64_t plan_useful(const hf_task* t, int waves) {
+  const hf::DevTask d = prepared(t, true);
+  return hf::useful_wgs(t, d, waves);
+}
+
+}  // extern "C"
