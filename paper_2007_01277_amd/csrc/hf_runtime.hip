@@ -162,6 +162,14 @@ void shutdown_all() {
   (void)hipSetDevice(cur);
 }
 
+// Size of a slot allocated for `bytes`: whole MiB, with room for what
+// own_scratch_bytes adds to scratch_bytes (at most 256 KiB for statistics, 18 KiB
+// for a histogram), so that a task whose scratch_bytes fits a slot's whole MiB
+// never grows it: growing is not possible while a stream is captured.
+size_t slot_bytes(size_t bytes) {
+  return std::max<size_t>((bytes + (1u << 20) - 1) & ~size_t((1u << 20) - 1), 1u << 20) + (512u << 10);
+}
+
 // Zero-filled library scratch for slot `i` of at least `bytes` bytes.
 int arena_slot(DeviceState* s, int i, size_t bytes, void** out) {
   if ((int)s->slots.size() <= i) s->slots.resize(i + 1);
@@ -172,11 +180,7 @@ int arena_slot(DeviceState* s, int i, size_t bytes, void** out) {
     if (sl.ptr) (void)hipFree(sl.ptr);
     sl.ptr = nullptr;
     sl.bytes = 0;
-    // with room for what own_scratch_bytes adds to scratch_bytes (at most 256 KiB and
-    // 18 KiB), so that a task whose scratch_bytes fits a slot's whole MiB never grows
-    // it: growing is not possible while a stream is captured
-    const size_t want =
-        std::max<size_t>((bytes + (1u << 20) - 1) & ~size_t((1u << 20) - 1), 1u << 20) + (512u << 10);
+    const size_t want = slot_bytes(bytes);
     if ((e = hipMalloc(&sl.ptr, want)) != hipSuccess) {
       record_hip(e);
       return HF_ENOMEM;
@@ -300,14 +304,19 @@ int64_t scratch_bytes(const hf_task* t) {
 // Statistics in the library's own scratch: log2 of the words from one arrival
 // counter to the next.  A 128-byte line for each of up to 2048 channels (256 KiB;
 // [76,16,56,56], whose 3728 arrivals otherwise queue on one line: 49 us packed, 10
-// in lines); more channels than that have arrivals on 64 lines and more as they are.
-static uint32_t own_ctr_shift(const hf_task* t) { return t->c <= 2048 ? 5u : 0u; }
+// in lines); more channels than that have arrivals on 64 lines and more as they
+// are, and channels handed out whole have none.
+static uint32_t own_ctr_shift(const hf_task* t) {
+  return t->c <= 2048 && !BnStats::whole_channels(bn_units(t), (uint32_t)t->c) ? 5u : 0u;
+}
 
 // Scratch of a task in the library's own memory: a histogram there gets all
 // its accumulators, statistics counters in lines of their own.
 size_t own_scratch_bytes(const hf_task* t) {
-  if (t->kind == HF_BN_STATS && scratch_bytes(t) > 0)
-    return (size_t)scratch_bytes(t) + 4 * ((size_t)t->c << own_ctr_shift(t));
+  if (t->kind == HF_BN_STATS && scratch_bytes(t) > 0) {
+    const uint32_t shift = own_ctr_shift(t);
+    return (size_t)scratch_bytes(t) + (shift ? 4 * ((size_t)t->c << shift) : 0);
+  }
   if (t->kind == HF_LDS_HIST) return 4 * (256 * (size_t)LdsHist::kSums + 32 * (1 + (size_t)LdsHist::kSums));
   return (size_t)std::max<int64_t>(scratch_bytes(t), 0);
 }

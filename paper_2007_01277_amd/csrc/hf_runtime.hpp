@@ -46,6 +46,7 @@ int validate_task(const hf_task* t);
 int validate_fused(const hf_pair* pr, const hf_config* cfg);
 int64_t scratch_bytes(const hf_task* t);
 size_t own_scratch_bytes(const hf_task* t);
+size_t slot_bytes(size_t bytes);
 int prepare(const hf_task* t, void* scratch, bool own, DevTask* dt);
 int arena_slot(DeviceState* s, int i, size_t bytes, void** out);
 int launch_solo(DeviceState* s, const hf_task* t, int block, int grid, int slot, hipStream_t st);

@@ -25,4 +25,9 @@ int64_t plan_useful(const hf_task* t, int waves) {
   return hf::useful_wgs(t, d, waves);
 }
 
+// Bytes of a task's scratch in the library's own memory, and of an arena slot
+// allocated for `bytes`.
+int64_t plan_own_scratch(const hf_task* t) { return (int64_t)hf::own_scratch_bytes(t); }
+int64_t plan_slot(int64_t bytes) { return (int64_t)hf::slot_bytes((size_t)bytes); }
+
 }  // extern "C"

@@ -22,7 +22,9 @@ def lib():
     L = ctypes.CDLL(SO)
     t = ctypes.POINTER(H.hf_task)
     for name, res, args in (("plan_wgs", ctypes.c_uint32, [t] + [ctypes.c_int] * 5),
-                            ("plan_useful", ctypes.c_int64, [t, ctypes.c_int])):
+                            ("plan_useful", ctypes.c_int64, [t, ctypes.c_int]),
+                            ("plan_own_scratch", ctypes.c_int64, [t]),
+                            ("plan_slot", ctypes.c_int64, [ctypes.c_int64])):
         f = getattr(L, name)
         f.restype, f.argtypes = res, args
     return L
@@ -51,3 +53,11 @@ def wgs(t, waves, block, resident, num_cus=256, own=True):
 
 def useful(t, waves):
     return lib().plan_useful(ctypes.byref(t), waves)
+
+
+def own_scratch(t):
+    return lib().plan_own_scratch(ctypes.byref(t))
+
+
+def slot(nbytes):
+    return lib().plan_slot(nbytes)

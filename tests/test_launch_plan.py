@@ -21,3 +21,35 @@ def test_a_launch_stays_below_2_to_the_32_lanes(t, block, per_cu):
         g = P.wgs(t, waves, block, 256 * per_cu)
         assert 1 <= g and g * block < 1 << 32, (waves, g)
         assert g <= P.useful(t, waves)
+
+
+def _extra(c, n, h, w):
+    t = P.task(H.HF_BN_STATS, (n, c, h, w))
+    return P.own_scratch(t) - H.hf_scratch_bytes(t)
+
+
+def test_statistics_scratch_grows_by_a_line_per_channel_or_not_at_all():
+    for c in (1, 16, 255, 2047, 2048):
+        assert _extra(c, 64, 56, 56) == 128 * c
+    for c in (2049, 65536, 131073, 174762, 200000):  # packed counters
+        assert _extra(c, 1, 60, 60) == 0
+    # whole channels count no arrivals
+    for c, n, h, w in ((2048, 1, 7, 7), (16, 2, 32, 32), (2048, 8, 32, 32), (256, 8, 32, 32)):
+        assert _extra(c, n, h, w) == 0
+    assert _extra(255, 8, 32, 32) == 128 * 255
+
+
+def test_a_task_that_fits_a_slot_s_mebibytes_never_grows_it():
+    """Growing is impossible while a stream is captured: whatever needs no more
+    whole MiB of hf_scratch_bytes than an earlier task must fit its slot."""
+    tasks = [P.task(H.HF_LDS_HIST, (1 << 20,), (256,))]
+    for c in (1, 100, 2047, 2048, 2049, 65537, 131073, 174762, 200000, 260000):
+        for hw in (1, 32, 47, 64, 97, 1000):
+            if c * hw * hw < 1 << 31:
+                tasks.append(P.task(H.HF_BN_STATS, (1, c, hw, hw)))
+    for a in tasks:
+        slot = P.slot(P.own_scratch(a))
+        mib = max(1, -(-H.hf_scratch_bytes(a) // (1 << 20))) << 20
+        for b in tasks:
+            if H.hf_scratch_bytes(b) <= mib:
+                assert P.own_scratch(b) <= slot, (a.kind, a.c, a.h, b.kind, b.c, b.h)
