@@ -41,7 +41,12 @@ __device__ __forceinline__ uint64_t op3(uint64_t a, uint64_t b, uint64_t c) {
 // 64-bit rotate takes two 64-bit shifts and two ORs.  A wave-uniform value (uni
 // true) keeps the plain form, which the scalar unit executes: the alignbit form
 // exists only as a vector instruction and would move uniform work, and the
-// registers that hold its results across the loop, to the vector unit.
+// registers that hold its results across the loop, to the vector unit.  PAIR: the
+// halves are joined as a register pair, which is what an addition of the result
+// wants (BLAKE2b); SHA-512's results meet only xors and three-term sums, and there
+// the or leaves the scheduler the halves (79 VGPRs next to sha256d, 104 with
+// pairs: six wavefronts per SIMD and four).
+template <bool PAIR = false>
 __device__ __forceinline__ uint64_t rotr64(uint64_t x, uint32_t n, bool uni = false) {
   if (uni) return __builtin_rotateright64(x, n);
   const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
@@ -56,12 +61,12 @@ __device__ __forceinline__ uint64_t rotr64(uint64_t x, uint32_t n, bool uni = fa
     rl = __builtin_amdgcn_alignbit(lo, hi, n - 32);
     rh = __builtin_amdgcn_alignbit(hi, lo, n - 32);
   }
-  return pair64(rl, rh);
+  return PAIR ? pair64(rl, rh) : ((uint64_t)rh << 32) | rl;
 }
 __device__ __forceinline__ uint64_t shr64(uint64_t x, uint32_t n, bool uni = false) {  // 0 < n < 32
   if (uni) return x >> n;
   const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
-  return pair64(__builtin_amdgcn_alignbit(hi, lo, n), hi >> n);
+  return ((uint64_t)(hi >> n) << 32) | __builtin_amdgcn_alignbit(hi, lo, n);
 }
 
 // ============================================================ SHA-256d
@@ -254,13 +259,13 @@ struct Blake2b {
   __device__ static __forceinline__ void G(uint64_t (&v)[16], int a, int b, int c, int d, uint64_t x, uint64_t y,
                                            bool u1 = false, bool u2 = false) {
     v[a] = v[a] + v[b] + x;
-    v[d] = rotr64(v[d] ^ v[a], 32, u1);
+    v[d] = rotr64<true>(v[d] ^ v[a], 32, u1);
     v[c] = v[c] + v[d];
-    v[b] = rotr64(v[b] ^ v[c], 24, u1);
+    v[b] = rotr64<true>(v[b] ^ v[c], 24, u1);
     v[a] = v[a] + v[b] + y;
-    v[d] = rotr64(v[d] ^ v[a], 16, u2);
+    v[d] = rotr64<true>(v[d] ^ v[a], 16, u2);
     v[c] = v[c] + v[d];
-    v[b] = rotr64(v[b] ^ v[c], 63, u2);
+    v[b] = rotr64<true>(v[b] ^ v[c], 63, u2);
   }
 
   template <class Bar>
@@ -347,8 +352,8 @@ struct Sha512 {
     return j <= 8 || (j >= 10 && j <= 15) || j == 17 || j == 19 || j == 21;
   }
 
-  __device__ static __forceinline__ uint64_t xor3(uint64_t a, uint64_t b, uint64_t c, bool uniform_words) {
-    return uniform_words ? a ^ b ^ c : op3<kXor3>(a, b, c);
+  __device__ static __forceinline__ uint64_t xor3(uint64_t a, uint64_t b, uint64_t c, bool plain) {
+    return plain ? a ^ b ^ c : op3<kXor3>(a, b, c);
   }
 
   // Sec. 6.4.2, rounds T0 .. T1-1 on the working variables v; w is the rolling
@@ -380,10 +385,13 @@ struct Sha512 {
         ku = kK[t] + wu;
         w[i] = wu + wv;
       }
-      const uint64_t S1 = xor3(rotr64(e, 14, us), rotr64(e, 18, us), rotr64(e, 41, us), us);
+      // S1 and S0 stay plain: as one operation each they lengthen the live ranges
+      // of all rotations (see rotr64) and gain nothing (sha256d and walks, split 3 of
+      // 4 at block 256, bound to 64 VGPRs: 591 us as one, 592 plain)
+      const uint64_t S1 = rotr64(e, 14, us) ^ rotr64(e, 18, us) ^ rotr64(e, 41, us);
       const uint64_t ch = us ? (e & f) ^ (~e & g) : op3<kCh>(e, f, g);
       const uint64_t T1v = ku + h + S1 + ch + wv;
-      const uint64_t S0 = xor3(rotr64(a, 28, us), rotr64(a, 34, us), rotr64(a, 39, us), us);
+      const uint64_t S0 = rotr64(a, 28, us) ^ rotr64(a, 34, us) ^ rotr64(a, 39, us);
       const uint64_t maj = us ? (a & b) ^ (a & c) ^ (b & c) : op3<kMaj>(a, b, c);
       h = g;
       g = f;
@@ -427,9 +435,6 @@ struct Sha512 {
 // Beyond, where HBM is busy with any split, 64 and packed (102013 walks next to a
 // histogram: 151 us spread, 144 packed).
 struct EthashLike {
-  // 78 VGPRs alone; next to some bodies the compiler takes 104 and four waves per
-  // SIMD (with sha256d, split 6 of 8, block 512: 708 us; at six waves 559)
-  static constexpr int kFusedWaves = 6;
   static constexpr uint32_t lds_words(int) { return 0; }
   static constexpr uint32_t kPrime = 16777619u;
   static constexpr uint32_t kChains = 4;

@@ -72,23 +72,8 @@ struct SoloWaves<K, std::void_t<decltype(K::kSoloWaves)>> {
   static constexpr int v = K::kSoloWaves;
 };
 
-// Waves per SIMD a fused kernel without a bound asks for (a body's kFusedWaves):
-// a body that the compiler, left alone, spreads over registers it does not need.
-template <class K, class = void>
-struct BodyWaves {
-  static constexpr int v = 1;
-};
-template <class K>
-struct BodyWaves<K, std::void_t<decltype(K::kFusedWaves)>> {
-  static constexpr int v = K::kFusedWaves;
-};
-template <class K1, class K2>
-constexpr int fused_waves() {
-  return BodyWaves<K1>::v > BodyWaves<K2>::v ? BodyWaves<K1>::v : BodyWaves<K2>::v;
-}
-
 template <class K1, class K2, int BLOCK>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(fused_waves<K1, K2>()))) fused_nocap(DevTask ta, DevTask tb, uint32_t w1, uint32_t g1,
+__global__ void __launch_bounds__(BLOCK) fused_nocap(DevTask ta, DevTask tb, uint32_t w1, uint32_t g1,
                                                      uint32_t g2) {
   fused_body<K1, K2, BLOCK>(ta, tb, w1, g1, g2);
 }
