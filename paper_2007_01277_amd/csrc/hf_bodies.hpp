@@ -381,6 +381,9 @@ struct BnStats {
     for (uint32_t k = 0; k < a.upc; ++k) {
       // the last unit again past the end, so that the loop has no branch
       load_unit<VEC>(a, c, min(k + 1u, a.upc - 1u) * kUnit, lane, nxt);
+      // one by one, the loads leave before this unit is reduced: mixed with it, their
+      // 16 addresses live on through it (bound to 64 VGPRs, 12 of them spilled)
+      if constexpr (!VEC) __builtin_amdgcn_sched_barrier(0);
       float mu, m2;
       unit_stats<VEC, false>(a, cur, k * kUnit, lane, mu, m2);
       mu_k = lane == k ? mu : mu_k;

@@ -27,3 +27,10 @@ def test_walk_pairs_without_a_bound_are_unbounded(kind, block):
 @pytest.mark.parametrize("block", [256, 512])
 def test_sha256d_next_to_walks_keeps_six_wavefronts_per_simd(block):
     assert H.hf_fused_info(H.HF_SHA256D, H.HF_ETHASH, block, 0)["waves_per_simd"] >= 6
+
+
+@pytest.mark.parametrize("block", [256, 512, 1024])
+@pytest.mark.parametrize("kind", [H.HF_INT_MIX, H.HF_IM2COL, H.HF_LDS_HIST, H.HF_UPSAMPLE, H.HF_SHA256D, H.HF_BLAKE2B])
+def test_statistics_bound_to_64_registers_do_not_spill(kind, block):
+    i = H.hf_fused_info(H.HF_BN_STATS, kind, block, 64)
+    assert i["spill_bytes"] == 0 and i["vgprs"] <= 64
