@@ -690,15 +690,28 @@ struct LdsHist {
     }
     bar.sync();
     if (uniform(lds[0]) == 0u) return;
-    const uint32_t used = min(p.nwg, a.sums);
     for (uint32_t b = p.lane; b < 256u; b += p.nlanes) {
-      uint32_t v[kSums], s = 0;  // every accumulator is requested before the first is used
+      uint32_t* q = a.acc + b;
+      uint32_t s = 0;
+      if (many) {
+        // in fours, up to the last that a workgroup added to (the others are zero, a
+        // condition each would be 16 lane masks and addresses in scalar registers);
+        // all are requested before the first is used
+        uint32_t v[kSums];
 #pragma unroll
-      for (uint32_t k = 0; k < kSums; ++k) v[k] = load_agent(a.acc + 256u * min(k, used - 1u) + b);
+        for (uint32_t k = 0; k < kSums; ++k) {
+          if (k % 4u == 0u && k >= p.nwg) break;
+          v[k] = load_agent(q + 256u * k);
+        }
 #pragma unroll
-      for (uint32_t k = 0; k < kSums; ++k) {
-        s += k < used ? v[k] : 0u;
-        if (k < used) store_agent(a.acc + 256u * k + b, 0u);
+        for (uint32_t k = 0; k < kSums; ++k) {
+          if (k % 4u == 0u && k >= p.nwg) break;
+          s += v[k];
+          store_agent(q + 256u * k, 0u);
+        }
+      } else {
+        s = load_agent(q);
+        store_agent(q, 0u);
       }
       a.out[b] = s;
     }

@@ -544,6 +544,14 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int block, i
     else  // one pass, to one wavefront of every workgroup first
       need = std::max<int64_t>(1, ((int64_t)d.eth.n + EthashLike::kPerPass - 1) / EthashLike::kPerPass);
   }
+  if (t->kind == HF_LDS_HIST) {
+    // each workgroup's start and merge take their time (9 MB next to 100001 blake2b
+    // nonces, split 4 of 16: 11.6 us on a workgroup per CU, 14.5 on two), and four
+    // wavefronts per CU keep the input streaming (2^26 bytes alone at block 256: 19.2
+    // us on one workgroup per CU, 18.4 on two, 19.0 on eight)
+    const int64_t enough = std::max<int64_t>(num_cus, (4 * num_cus + waves - 1) / waves);
+    need = std::min(need, enough);
+  }
   const bool stream = (t->kind == HF_UPSAMPLE || t->kind == HF_MAXPOOL) && resident >= 2 * num_cus;
   // a launch has fewer than 2^32 lanes; the bodies are grid-stride loops
   const int64_t most = stream ? (int64_t)(UINT32_MAX / (uint32_t)block) : resident;

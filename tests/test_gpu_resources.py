@@ -34,3 +34,8 @@ def test_sha256d_next_to_walks_keeps_six_wavefronts_per_simd(block):
 def test_statistics_bound_to_64_registers_do_not_spill(kind, block):
     i = H.hf_fused_info(H.HF_BN_STATS, kind, block, 64)
     assert i["spill_bytes"] == 0 and i["vgprs"] <= 64
+
+
+@pytest.mark.parametrize("kind", [H.HF_INT_MIX, H.HF_IM2COL, H.HF_BLAKE2B])
+def test_histogram_pairs_fit_two_workgroups_of_1024_on_a_cu(kind):
+    assert H.hf_fused_info(min(kind, H.HF_LDS_HIST), max(kind, H.HF_LDS_HIST), 1024, 0)["wg_per_cu"] == 2

@@ -53,3 +53,16 @@ def test_a_task_that_fits_a_slot_s_mebibytes_never_grows_it():
         for b in tasks:
             if H.hf_scratch_bytes(b) <= mib:
                 assert P.own_scratch(b) <= slot, (a.kind, a.c, a.h, b.kind, b.c, b.h)
+
+
+@pytest.mark.parametrize("n", [1, 1000, 1 << 16, 1 << 20, 9_000_001, 1 << 26, (1 << 31) - 1])
+@pytest.mark.parametrize("block,per_cu", [(256, 8), (512, 4), (1024, 2)])
+def test_a_histogram_takes_four_wavefronts_per_cu(n, block, per_cu):
+    """However many workgroups the launch has room for, each starts and merges."""
+    t = P.task(H.HF_LDS_HIST, (n,), (256,))
+    for waves in (1, 2, block // 64):
+        g = P.wgs(t, waves, block, 256 * per_cu)
+        assert 1 <= g <= min(P.useful(t, waves), 256 * per_cu)
+        assert g <= max(256, -(-1024 // waves))
+        if n >= 1 << 20:
+            assert g * waves >= 1024 or g == 256 * per_cu
