@@ -969,33 +969,46 @@ struct Upsample {
       where(u, plane, y0, col);
       const bool first = col == 0u, last = col + 2u >= W, top = y0 == 0u;
       const __amdgpu_buffer_rsrc_t dst = buffer_rsrc(a.out + (size_t)plane * OHW, 4u * OHW);
-      float h[kBand + 2][4];
-#pragma unroll
-      for (uint32_t i = 0; i < kBand + 2u; ++i) {
-        // every lane takes part in the shifts (row_shr:1 / row_shl:1)
+      // the four columns of input row i; every lane takes part in the shifts
+      // (row_shr:1 / row_shl:1)
+      auto row = [&](uint32_t i, float (&h)[4]) {
         const float sl = dpp_f32<0x111>(r.x[i].y), sr = dpp_f32<0x101>(r.x[i].x);
         const float p0 = first ? r.x[i].x : (c4 == 0u ? r.e[i] : sl), p1 = r.x[i].x, p2 = r.x[i].y;
         const float p3 = last ? r.x[i].y : (c4 == 15u ? r.e[i] : sr);
-        h[i][0] = lerp(p0, p1, 0.75f);
-        h[i][1] = lerp(p1, p2, 0.25f);
-        h[i][2] = lerp(p1, p2, 0.75f);
-        h[i][3] = lerp(p2, p3, 0.25f);
-      }
-#pragma unroll
-      for (uint32_t o = 0; o < 2u * kBand; ++o) {
-        // output row 2y lies between input rows y-1 and y (the image's first row
-        // is input row 0 with weight 0 on row 1), output row 2y+1 between y and y+1
-        const uint32_t i = o / 2u + (o & 1u);
-        float v[4];
-#pragma unroll
-        for (uint32_t c = 0; c < 4u; ++c) {
-          if (o == 0u)
-            v[c] = lerp(top ? h[1][c] : h[0][c], top ? h[2][c] : h[1][c], top ? 0.f : 0.75f);
-          else
-            v[c] = lerp(h[i][c], h[i + 1u][c], (o & 1u) ? 0.25f : 0.75f);
-        }
+        h[0] = lerp(p0, p1, 0.75f);
+        h[1] = lerp(p1, p2, 0.25f);
+        h[2] = lerp(p1, p2, 0.75f);
+        h[3] = lerp(p2, p3, 0.25f);
+      };
+      auto out = [&](uint32_t o, const float (&t)[4], const float (&b)[4], float l) {
         const uint32_t oy = 2u * y0 + o;
-        buffer_store4_nt(dst, oy < a.Ho && col < W ? 4u * (oy * a.Wo + 2u * col) : kOutOfRange, v[0], v[1], v[2], v[3]);
+        buffer_store4_nt(dst, oy < a.Ho && col < W ? 4u * (oy * a.Wo + 2u * col) : kOutOfRange, lerp(t[0], b[0], l),
+                         lerp(t[1], b[1], l), lerp(t[2], b[2], l), lerp(t[3], b[3], l));
+      };
+      // output row 2y lies between input rows y-1 and y (the image's first row is
+      // input row 0 with weight 0 on row 1), output row 2y+1 between y and y+1; of
+      // the rows only two are held at a time
+      float h[3][4];
+      row(0u, h[0]);
+      row(1u, h[1]);
+#pragma unroll
+      for (uint32_t i = 1; i < kBand + 1u; ++i) {
+        float(&t)[4] = h[i % 3u], (&b)[4] = h[(i + 1u) % 3u];
+        row(i + 1u, b);
+        if (i == 1u) {
+          float z[4], w[4];
+#pragma unroll
+          for (uint32_t c = 0; c < 4u; ++c) {
+            z[c] = top ? t[c] : h[0][c];
+            w[c] = top ? b[c] : t[c];
+          }
+          out(0u, z, w, top ? 0.f : 0.75f);
+        }
+        out(2u * i - 1u, t, b, 0.25f);
+        if (i < kBand) out(2u * i, t, b, 0.75f);
+        // as written: the scheduler, left alone, computes every row before the first
+        // store and takes 70 VGPRs for 64, a wavefront per SIMD less
+        __builtin_amdgcn_sched_barrier(0);
       }
     };
     // the next unit is requested before this one is stored: the vector-memory

@@ -39,3 +39,9 @@ def test_statistics_bound_to_64_registers_do_not_spill(kind, block):
 @pytest.mark.parametrize("kind", [H.HF_INT_MIX, H.HF_IM2COL, H.HF_BLAKE2B])
 def test_histogram_pairs_fit_two_workgroups_of_1024_on_a_cu(kind):
     assert H.hf_fused_info(min(kind, H.HF_LDS_HIST), max(kind, H.HF_LDS_HIST), 1024, 0)["wg_per_cu"] == 2
+
+
+def test_upsample_fits_eight_wavefronts_on_a_simd():
+    for block in (256, 512, 1024):
+        assert H.hf_solo_info(H.HF_UPSAMPLE, block)["waves_per_simd"] == 8
+        assert H.hf_fused_info(H.HF_LDS_HIST, H.HF_UPSAMPLE, block, 0)["waves_per_simd"] == 8
