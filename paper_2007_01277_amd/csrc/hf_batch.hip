@@ -60,7 +60,9 @@ __device__ __forceinline__ void run_body(int kind, const DevTask& t, const Part&
         switch (kind) {
           case HF_SHA256D: Sha256d::run(t, p, bar, mid); break;
           case HF_BLAKE2B: Blake2b::run(t, p, bar, lds); break;
-          case HF_ETHASH: EthashLike::run(t, p, bar, lds); break;
+          // next to the other bodies the three-input xors of the early schedule words
+          // cost 15 VGPRs more than there are (72 bytes of spills per lane)
+          case HF_ETHASH: EthashLike::run<40>(t, p, bar, lds); break;
           default: break;
         }
       }

@@ -362,7 +362,8 @@ struct Sha512 {
   // uniform values (the caller runs them once per wavefront).  The uniform
   // terms of a schedule word are summed first and with the round constant, so
   // that they form one loop-invariant value.
-  template <int T0, int T1>
+  // Schedule words below PLAIN keep the plain xors (see the batch kernels).
+  template <int T0, int T1, int PLAIN = 0>
   __device__ static __forceinline__ void rounds(uint64_t (&v)[8], uint64_t (&w)[16]) {
     uint64_t a = v[0], b = v[1], c = v[2], d = v[3], e = v[4], f = v[5], g = v[6], h = v[7];
 #pragma unroll
@@ -376,8 +377,8 @@ struct Sha512 {
         const int i = t & 15;
         const uint64_t x = w[(i + 1) & 15], y = w[(i + 14) & 15];
         const bool ux = uni(t - 15), uy = uni(t - 2);
-        const uint64_t s0 = xor3(rotr64(x, 1, ux), rotr64(x, 8, ux), shr64(x, 7, ux), ux);
-        const uint64_t s1 = xor3(rotr64(y, 19, uy), rotr64(y, 61, uy), shr64(y, 6, uy), uy);
+        const uint64_t s0 = xor3(rotr64(x, 1, ux), rotr64(x, 8, ux), shr64(x, 7, ux), ux || t < PLAIN);
+        const uint64_t s1 = xor3(rotr64(y, 19, uy), rotr64(y, 61, uy), shr64(y, 6, uy), uy || t < PLAIN);
         const uint64_t q = w[(i + 9) & 15], r = w[i];
         const bool uq = uni(t - 7), ur = uni(t - 16);
         const uint64_t wu = (uy ? s1 : 0) + (uq ? q : 0) + (ux ? s0 : 0) + (ur ? r : 0);
@@ -448,7 +449,7 @@ struct EthashLike {
     return ((uint64_t)__builtin_bswap32(hdr[2 * k]) << 32) | __builtin_bswap32(hdr[2 * k + 1]);
   }
 
-  template <class Bar>
+  template <int PLAIN = 0, class Bar>
   __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
     const EthArgs& a = dt.eth;
     if (a.n == 0) return;
@@ -483,11 +484,11 @@ struct EthashLike {
 #pragma unroll
         for (int k = 11; k < 15; ++k) w[k] = 0;
         w[15] = 640;
-        Sha512::rounds<9, 16>(v, w);
-        Sha512::rounds<16, 32>(v, w);
-        Sha512::rounds<32, 48>(v, w);
-        Sha512::rounds<48, 64>(v, w);
-        Sha512::rounds<64, 80>(v, w);
+        Sha512::rounds<9, 16, PLAIN>(v, w);
+        Sha512::rounds<16, 32, PLAIN>(v, w);
+        Sha512::rounds<32, 48, PLAIN>(v, w);
+        Sha512::rounds<48, 64, PLAIN>(v, w);
+        Sha512::rounds<64, 80, PLAIN>(v, w);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
           const uint64_t hk = Sha512::h0(k) + v[k];
