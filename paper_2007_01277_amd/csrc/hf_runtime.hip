@@ -421,17 +421,28 @@ int prepare(const hf_task* t, void* scratch, bool own, DevTask* dt) {
       a.s = s;
       // by places: the coordinates of neighbouring outputs have to keep their
       // distance, which float32 grants below 2^22; four outputs lie between four
-      // input columns from scale 3 on
-      a.places = (!a.vec || s >= 3u) && a.Ho < (1u << 22) && a.Wo < (1u << 22)
+      // input columns from scale 3 on.  A lane's s rows go out one store after the
+      // other, which leaves a line that several short rows share to be completed by
+      // a later store: below 6 columns (8 at scale 3) of rows that are no whole
+      // lines the pointwise path, which stores front to back, is faster (places and
+      // pointwise, block 256, 67 to 105 MB: 4x4 x3 71 and 42 us, 7x7 x3 56 and 52,
+      // 8x8 x3 37 and 47; 3x3 x4 67 and 23, 6x6 x4 37 and 48; 4x4 x5 56 and 24, 7x7
+      // x5 47 and 81; 5x5 x8 35 and 29, 4x4 x8 18 and 22).
+      const bool long_rows = s <= 2u || a.W >= (s == 3u ? 8u : 6u) || a.Wo % 32u == 0u;
+      a.places = (!a.vec || s >= 3u) && long_rows && a.Ho < (1u << 22) && a.Wo < (1u << 22)
                      ? (uint32_t)t->n * (uint32_t)t->c * a.H * rowlen
                      : 0u;
       a.div_group = make_fastdiv(a.H * rowlen);
-      // the row path addresses one input and one output plane through buffer
-      // resources of < 2^31 bytes
-      a.row2 = s == 2u && a.W % 2u == 0u && (uint64_t)a.Ho * a.Wo * 4u < (1ull << 31) && aligned(t->in, 8) &&
-               aligned(t->out0, 16);
       a.nch = (a.W + 31u) / 32u;
       a.nq = (uint32_t)(((uint64_t)((a.H + Upsample::kBand - 1u) / Upsample::kBand) * a.nch + 3u) / 4u);
+      // the row path addresses one input and one output plane through buffer
+      // resources of < 2^31 bytes.  Its unit has lanes for four chunks of 32 columns
+      // and kBand rows: planes that leave more than half of them idle take the
+      // pointwise path, whose lanes small planes fill (rows and pointwise, 134 MB
+      // written, block 256: 4x4 307 and 41 us, 8x8 80 and 41, 12x12 65 and 42, 16x16
+      // 35 and 42, 24x24 40 and 44, 32x32 35 and 43).
+      a.row2 = s == 2u && a.W % 2u == 0u && (uint64_t)a.Ho * a.Wo * 4u < (1ull << 31) && aligned(t->in, 8) &&
+               aligned(t->out0, 16) && 2ull * a.H * a.W >= 4ull * 32u * Upsample::kBand * a.nq;
       a.row_units = (uint32_t)t->n * (uint32_t)t->c * a.nq;
       a.div_nq = make_fastdiv(a.nq);
       a.div_nch = make_fastdiv(a.nch);
@@ -494,6 +505,12 @@ int prepare(const hf_task* t, void* scratch, bool own, DevTask* dt) {
 // with four; 2x2 over [29,32,56,56] fits the chip: 12 us with one, 15 with four).
 constexpr int64_t kPoolUnits = 4;
 
+// Outputs of the upsampling paths by places and pointwise that a wavefront takes
+// at least, once the resident workgroups are busy (scale 1 over 6x7 planes, 55 M
+// outputs, at block 512: 156 us with 64 each, 118 with 256).  The row path's units
+// have 2048.
+constexpr int64_t kUpOutputs = 256;
+
 // Workgroups that still find work when the task runs on `waves` wavefronts per
 // workgroup (1 for an empty task).
 int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves) {
@@ -531,6 +548,11 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int block, i
   int64_t need = useful_wgs(t, d, waves);
   if (t->kind == HF_MAXPOOL && !d.pool.row3)
     need = std::max(std::min<int64_t>(need, resident), (need + kPoolUnits - 1) / kPoolUnits);
+  if (t->kind == HF_UPSAMPLE && !d.up.row2) {
+    const int64_t per = (d.up.vec ? 4 : 1) * (d.up.places ? 64ll * d.up.s : (int64_t)d.up.lanes_per_unit);
+    const int64_t units = std::max<int64_t>(1, kUpOutputs / per);
+    need = std::max(std::min<int64_t>(need, resident), (need + units - 1) / units);
+  }
   // bodies that spread their wavefronts' work over the workgroups (wave_index, whole
   // channels): a workgroup for every CU before a second wavefront of any (1000
   // sha256d nonces at block 256, 512 and 1024: 9.4, 16 and 29 us packed into 4, 2
@@ -552,7 +574,11 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int block, i
     const int64_t enough = std::max<int64_t>(num_cus, (4 * num_cus + waves - 1) / waves);
     need = std::min(need, enough);
   }
-  const bool stream = (t->kind == HF_UPSAMPLE || t->kind == HF_MAXPOOL) && resident >= 2 * num_cus;
+  // (upsample's short units need those gaps covered better still: 12x12 x2 by
+  // points, 47 M outputs, block 1024, two workgroups per CU: 64 us in order, 44
+  // resident)
+  const bool stream = (t->kind == HF_UPSAMPLE || t->kind == HF_MAXPOOL) &&
+                      resident >= (t->kind == HF_UPSAMPLE && !d.up.row2 ? 3 : 2) * num_cus;
   // a launch has fewer than 2^32 lanes; the bodies are grid-stride loops
   const int64_t most = stream ? (int64_t)(UINT32_MAX / (uint32_t)block) : resident;
   return (uint32_t)std::min<int64_t>(need, most);

@@ -30,4 +30,10 @@ int64_t plan_useful(const hf_task* t, int waves) {
 int64_t plan_own_scratch(const hf_task* t) { return (int64_t)hf::own_scratch_bytes(t); }
 int64_t plan_slot(int64_t bytes) { return (int64_t)hf::slot_bytes((size_t)bytes); }
 
+// Path of an upsample: 2 rows, 1 places, 0 pointwise.
+int plan_upsample_path(const hf_task* t) {
+  const hf::DevTask d = prepared(t, true);
+  return d.up.row2 ? 2 : d.up.places ? 1 : 0;
+}
+
 }  // extern "C"

@@ -24,7 +24,7 @@ def lib():
     for name, res, args in (("plan_wgs", ctypes.c_uint32, [t] + [ctypes.c_int] * 5),
                             ("plan_useful", ctypes.c_int64, [t, ctypes.c_int]),
                             ("plan_own_scratch", ctypes.c_int64, [t]),
-                            ("plan_slot", ctypes.c_int64, [ctypes.c_int64])):
+                            ("plan_slot", ctypes.c_int64, [ctypes.c_int64]), ("plan_upsample_path", ctypes.c_int, [t])):
         f = getattr(L, name)
         f.restype, f.argtypes = res, args
     return L
@@ -61,3 +61,7 @@ def own_scratch(t):
 
 def slot(nbytes):
     return lib().plan_slot(nbytes)
+
+
+def upsample_path(t):
+    return lib().plan_upsample_path(ctypes.byref(t))

@@ -66,3 +66,34 @@ def test_a_histogram_takes_four_wavefronts_per_cu(n, block, per_cu):
         assert g <= max(256, -(-1024 // waves))
         if n >= 1 << 20:
             assert g * waves >= 1024 or g == 256 * per_cu
+
+
+def test_upsample_takes_the_path_whose_lanes_the_planes_fill():
+    """Rows: an even width whose chunks of 32 columns and bands of four rows keep half
+    of a unit's lanes; places: rows long enough, or whole lines; else pointwise."""
+    def path(h, w, s, misalign=0, planes=32):
+        return P.upsample_path(P.task(H.HF_UPSAMPLE, (1, planes, h, w), (s,), misalign))
+
+    for h, w in ((1, 2), (2, 2), (4, 4), (8, 8), (12, 12), (1, 96), (4096, 4)):
+        assert path(h, w, 2) == 0, (h, w)
+    for h, w in ((16, 16), (24, 24), (32, 32), (28, 28), (56, 56), (3, 96), (4, 64), (128, 128)):
+        assert path(h, w, 2) == 2, (h, w)
+    assert path(16, 16, 2, misalign=4) == 1  # one output column at a time
+    assert path(16, 17, 2) == 1
+    for s, short, full in ((3, 7, 8), (4, 5, 6), (5, 5, 6), (16, 5, 6)):
+        assert path(9, short, s) == 0 and path(9, full, s) == 1, s
+    assert path(9, 4, 8) == 1 and path(9, 2, 16) == 1  # whole lines
+    assert path(9, 3, 8) == 0
+    for s in (3, 4):  # past 2^22 the coordinates lose what the path by places assumes
+        assert path((1 << 22) // s + 1, 8, s, planes=1) == 0
+
+
+def test_short_upsample_units_are_taken_several_at_a_time():
+    for shape, s in (((1000, 64, 6, 7), 1), ((1000, 64, 5, 5), 2), ((2000, 64, 4, 4), 2)):
+        t = P.task(H.HF_UPSAMPLE, shape, (s,))
+        outputs = shape[0] * shape[1] * shape[2] * shape[3] * s * s
+        for block, per_cu in ((256, 8), (512, 4)):
+            W = block // 64
+            g = P.wgs(t, W, block, 256 * per_cu)
+            assert g <= outputs / (192 * W) and g > 256 * per_cu
+        assert P.wgs(t, 16, 1024, 512) <= 512  # their gaps are not covered: resident
