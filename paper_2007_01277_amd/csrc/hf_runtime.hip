@@ -574,6 +574,15 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int block, i
     const int64_t enough = std::max<int64_t>(num_cus, (4 * num_cus + waves - 1) / waves);
     need = std::min(need, enough);
   }
+  // arrivals of statistics whose counters share lines (the caller's scratch) are
+  // served one after the other: fewer wavefronts, with four units each or more, have
+  // fewer ([32,16,128,128], caller's scratch, block 512: 77 us on the resident
+  // workgroups, 32)
+  if (t->kind == HF_BN_STATS && d.bn.ctr_shift == 0u && d.bn.C <= 2048u &&
+      !BnStats::whole_channels(d.bn.upc, d.bn.C)) {
+    const int64_t ws = std::min<int64_t>(std::max<int64_t>(d.bn.total / 4u, 8 * num_cus), 16 * num_cus);
+    need = std::min<int64_t>(need, (ws + waves - 1) / waves);
+  }
   // (upsample's short units need those gaps covered better still: 12x12 x2 by
   // points, 47 M outputs, block 1024, two workgroups per CU: 64 us in order, 44
   // resident)
