@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -530,6 +531,39 @@ int64_t useful_wgs(const hf_task* t, const DevTask& d, int waves) {
   return std::max<int64_t>(units, 1);
 }
 
+// Workgroups of a table walk.  One pass per wavefront, to one wavefront of every
+// workgroup first, or two passes, packed (see EthashLike): the choice with the
+// least work on the busiest SIMD.  A workgroup of up to four busy wavefronts puts
+// one on each of that many SIMDs, successive workgroups of a CU go round them, and
+// more busy wavefronts double up.  Two passes take nearly twice as long as one (64
+// seeds are made either way), rather more where the rows come from HBM.  Walks of a
+// table in the L2 caches, us at block 256 and 512: on the resident workgroups in one
+// pass, packed in two, and as chosen here: 50000 51 and 50, 47 and 61, 41 and 39;
+// 95000 65 and 52, 65 and 62, 55 and 53; 130000 79 and 77, 68 and 65, 63 and 60;
+// 150000 80 and 90, 88 and 105, 82 and 92.
+static int64_t walk_wgs(int64_t n, uint32_t rows, int waves, int resident, int num_cus) {
+  const double two_passes = rows <= (4u << 20) / 128u ? 1.95 : 2.1;
+  const int64_t one = std::max<int64_t>((n + EthashLike::kPerPass - 1) / EthashLike::kPerPass, 1);
+  const int64_t two = (n + EthashLike::kPerIter - 1) / EthashLike::kPerIter;
+  const int per_cu = resident / num_cus;
+  const int64_t even = (int64_t)num_cus * (per_cu >= 4 ? 4 : per_cu >= 2 ? 2 : 1);
+  auto load = [&](double wgs_per_cu, double busy) {  // of the busiest SIMD
+    return std::max(1.0, wgs_per_cu * (busy <= 4.0 ? busy / 4.0 : std::ceil(busy / 4.0)));
+  };
+  const int64_t packed = std::max<int64_t>(std::min<int64_t>((two + waves - 1) / waves, resident), 1);
+  int64_t best = packed;
+  double least = two_passes * load(std::ceil((double)packed / num_cus), waves);
+  for (const int64_t wgs : {(int64_t)resident, even, one}) {
+    if (wgs > resident || one > wgs * waves) continue;  // not one pass each
+    const double l = load((double)wgs / num_cus, (double)one / (double)wgs);
+    if (l <= least) {
+      least = l;
+      best = wgs;
+    }
+  }
+  return best;
+}
+
 // Workgroups a task runs on by default, `waves` wavefronts of each of `block`
 // lanes, where `resident` workgroups fit the chip at once.  Upsample and maxpool stream
 // through HBM and get a workgroup for every unit of work, however many that is:
@@ -560,12 +594,7 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int block, i
   const bool spread = t->kind == HF_INT_MIX || t->kind == HF_SHA256D || t->kind == HF_BLAKE2B ||
                       (t->kind == HF_BN_STATS && BnStats::whole_channels(d.bn.upc, d.bn.C));
   if (spread) need = std::max(need, std::min<int64_t>(useful_wgs(t, d, 1), num_cus));
-  if (t->kind == HF_ETHASH) {
-    if (need > resident)  // two passes per wavefront, packed
-      need = (need + 1) / 2;
-    else  // one pass, to one wavefront of every workgroup first
-      need = std::max<int64_t>(1, ((int64_t)d.eth.n + EthashLike::kPerPass - 1) / EthashLike::kPerPass);
-  }
+  if (t->kind == HF_ETHASH) need = walk_wgs(d.eth.n, d.eth.rows.d, waves, resident, num_cus);
   if (t->kind == HF_LDS_HIST) {
     // each workgroup's start and merge take their time (9 MB next to 100001 blake2b
     // nonces, split 4 of 16: 11.6 us on a workgroup per CU, 14.5 on two), and four

@@ -113,3 +113,31 @@ def test_statistics_with_shared_counter_lines_arrive_less_often():
     assert P.wgs(P.task(H.HF_BN_STATS, big), 8, 512, 768) == 768
     few = P.task(H.HF_BN_STATS, (8, 32, 16, 16), scratch=True)  # whole channels: no counters
     assert P.wgs(few, 4, 256, 1792, own=False) == P.wgs(few, 4, 256, 1792)
+
+
+@pytest.mark.parametrize("rows", [4099, 1 << 23])
+@pytest.mark.parametrize("waves,block,per_cu", [(4, 256, 6), (1, 256, 6), (8, 512, 3), (2, 512, 2), (16, 1024, 1)])
+def test_table_walks_get_wavefronts_for_one_pass_or_two(rows, waves, block, per_cu):
+    res = 256 * per_cu
+    for n in (0, 1, 31, 33, 1000, 8192, 20000, 49152, 50000, 65000, 98304, 98305, 130000, 131073, 150000, 262144, 1 << 24):
+        t = P.task(H.HF_ETHASH, (n, 0, rows, 0))
+        g = P.wgs(t, waves, block, res)
+        assert 1 <= g <= res
+        one = -(-n // 32)
+        if one <= g * waves:  # one pass each
+            assert g <= max(1, one)
+        else:  # two passes, in no more iterations than the resident workgroups need
+            assert g == min(res, -(-n // (64 * waves)))
+
+
+def test_table_walks_load_the_simds_evenly():
+    def g(n, waves, block, per_cu, rows=4099):
+        return P.wgs(P.task(H.HF_ETHASH, (n, 0, rows, 0)), waves, block, 256 * per_cu)
+
+    assert g(20000, 8, 512, 3) == 625       # a workgroup for each wavefront
+    assert g(50000, 4, 256, 6) == 1024      # four per CU, not the six that fit
+    assert g(50000, 8, 512, 3) == 512
+    assert g(95000, 8, 512, 3) == 768       # four busy wavefronts in each of three
+    assert g(130000, 4, 256, 6) == 508      # two passes where the seeds count ...
+    assert g(130000, 4, 256, 6, 1 << 23) == 1024
+    assert g(130000, 16, 1024, 1) == 256    # ... unless CUs would idle
