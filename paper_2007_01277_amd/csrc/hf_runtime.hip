@@ -614,9 +614,11 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int block, i
   }
   // (upsample's short units need those gaps covered better still: 12x12 x2 by
   // points, 47 M outputs, block 1024, two workgroups per CU: 64 us in order, 44
-  // resident)
+  // resident; and for a few rounds of pooling workgroups order gains less than the
+  // gaps cost: 3x3 / stride 2 over [64,64,56,56], 21 and 19 us)
   const bool stream = (t->kind == HF_UPSAMPLE || t->kind == HF_MAXPOOL) &&
-                      resident >= (t->kind == HF_UPSAMPLE && !d.up.row2 ? 3 : 2) * num_cus;
+                      resident >= (t->kind == HF_UPSAMPLE && !d.up.row2 ? 3 : 2) * num_cus &&
+                      (t->kind == HF_UPSAMPLE || need >= 4 * (int64_t)resident);
   // a launch has fewer than 2^32 lanes; the bodies are grid-stride loops
   const int64_t most = stream ? (int64_t)(UINT32_MAX / (uint32_t)block) : resident;
   return (uint32_t)std::min<int64_t>(need, most);

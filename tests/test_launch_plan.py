@@ -141,3 +141,13 @@ def test_table_walks_load_the_simds_evenly():
     assert g(130000, 4, 256, 6) == 508      # two passes where the seeds count ...
     assert g(130000, 4, 256, 6, 1 << 23) == 1024
     assert g(130000, 16, 1024, 1) == 256    # ... unless CUs would idle
+
+
+def test_pooling_streams_from_four_rounds_of_workgroups_on():
+    def g(n, block=256, per_cu=8):
+        t = P.task(H.HF_MAXPOOL, (n, 64, 56, 56), (3, 3, 2, 1))
+        return P.wgs(t, 4, block, 256 * per_cu), P.useful(t, 4)
+
+    assert g(32)[0] == 2048 < g(32)[1]      # 1.75 rounds: resident
+    assert g(128)[0] == 2048 * 7            # seven: one for every unit
+    assert g(128, 1024, 1)[0] == 256
