@@ -143,7 +143,7 @@ typedef struct {
  *   grid         workgroups per launch, for both tasks; 0 = the default: each task
  *                its own number of workgroups (the resident ones, or one for every
  *                unit of work of a kernel that streams through memory), the launch
- *                the larger of the two.                                      */
+ *                the larger of the two.  A grid > 0 holds for both bodies.    */
 typedef struct {
   int32_t split_waves;
   int32_t block;
@@ -233,7 +233,10 @@ typedef struct {
   int32_t wg_per_cu;      /* resident workgroups per CU at this block size           */
   int32_t waves_per_simd; /* resident wavefronts per SIMD                            */
   int32_t num_cus;        /* compute units of the device                             */
-  int32_t default_grid;   /* workgroups resident on the device at once               */
+  int32_t default_grid;   /* the occupancy grid: workgroups resident on the device at
+                             once.  hf_run_* with grid == 0 launches this many, fewer
+                             where a task has less work or is faster on fewer, or (hf_run_solo,
+                             hf_run_fused*: upsample, maxpool) one for every unit of work */
 } hf_kernel_info;
 /* Resources of the fused instantiation for (pair kinds, block, cap). */
 int hf_fused_info(int kind_a, int kind_b, int block, int vgpr_cap, hf_kernel_info* out);
@@ -257,7 +260,8 @@ enum {
                              every body here is a grid-stride loop, so the grid is
                              free, and a grid larger than the resident workgroups
                              lets a workgroup whose partitions finish at different
-                             times leave its CU to the next one                     */
+                             times leave its CU to the next one.  Such a grid holds
+                             for both bodies, where the default gives each its own  */
 };
 typedef struct {
   int32_t n_candidates;   /* candidates the method considered                        */
@@ -401,9 +405,12 @@ int hf_batch_tune(const hf_task* tasks, int ntask, const int32_t* group_of_task,
  *                   whole-workgroup barrier between items.  The queue holds
  *                   the members of each group interleaved item by item, the
  *                   groups in order of decreasing estimated work.
- *   item_kb         estimated traffic of one work item, KiB (0: 256): the
+ *   item_kb         estimated traffic of one work item at most, KiB (0: 256): the
  *                   virtual grid of a task is its traffic over this, capped by
- *                   the workgroups that find work.
+ *                   the workgroups that find work.  A batch that would not give
+ *                   every resident worker two such items is cut finer, down to
+ *                   16 KiB per wavefront of a static item and 32 KiB per
+ *                   wavefront of a worker; sizes above that cut it alike.
  *   split_policy    static schedule without waves_of_task: 0 = wavefronts in
  *                   proportion to each member's estimated cost, 1 = even. */
 typedef struct {
@@ -420,7 +427,8 @@ int hf_batch_create_sched(const hf_task* tasks, int ntask, const int32_t* group_
 /* Schedule search over both kinds of schedule: static (blocks 256/512/1024 x
  * split policy x items of 128/256/512 KiB) and worker intervals (blocks x
  * intervals of 1/2/4/8 wavefronts x items of 64/128/256/512 KiB), every
- * schedule the batch admits profiled as the median of `reps` launches.
+ * schedule the batch admits profiled as the median of `reps` launches, also
+ * where several item sizes cut a small batch alike.
  * Writes the fastest schedule, its median time and the number profiled. */
 int hf_batch_tune_sched(const hf_task* tasks, int ntask, const int32_t* group_of_task, int reps, void* stream,
                         hf_batch_schedule* best_out, float* ms_out, int32_t* n_profiled);

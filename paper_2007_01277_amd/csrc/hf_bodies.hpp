@@ -1026,7 +1026,8 @@ struct Upsample {
     store(u, cur);
   }
 
-  // Path by places (any other scale; not float4 stores below scale 3): a place is
+  // Path by places (any other scale; not float4 stores below scale 3, nor short rows
+  // that are no whole lines): a place is
   // a plane, a group of the s output rows s*g .. s*g+s-1, and four adjacent output
   // columns (V = 4) or one.  Its rows lie between three consecutive input rows,
   // its columns between NC consecutive input columns: V = 1 two, V = 4 three from

@@ -434,7 +434,8 @@ struct Sha512 {
 // at block 256, 512 and 1024, 64 packed and 32 spread: 16000 walks 95, 106, 162 and
 // 51 us; 40000 walks 111, 121, 185 and 76; 81000 walks 143, 145, 200 and 115.
 // Beyond, where HBM is busy with any split, 64 and packed (102013 walks next to a
-// histogram: 151 us spread, 144 packed).
+// histogram: 151 us spread, 144 packed).  Which of the two a launch gets is decided
+// with its number of workgroups (walk_wgs).
 struct EthashLike {
   static constexpr uint32_t lds_words(int) { return 0; }
   static constexpr uint32_t kPrime = 16777619u;
