@@ -124,6 +124,8 @@ __device__ __forceinline__ void buffer_store4_nt(__amdgpu_buffer_rsrc_t r, uint3
 struct WGBarrier {
   __device__ __forceinline__ void sync() { __syncthreads(); }
 };
+// The same in a kernel that has no other body.
+struct SoloBarrier : WGBarrier {};
 
 // Arrival counter in LDS, monotonically increasing during one launch.  The k-th
 // barrier of an interval of W wavefronts completes when the counter reaches k*W.

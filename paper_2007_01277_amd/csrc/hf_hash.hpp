@@ -43,9 +43,9 @@ __device__ __forceinline__ uint64_t op3(uint64_t a, uint64_t b, uint64_t c) {
 // exists only as a vector instruction and would move uniform work, and the
 // registers that hold its results across the loop, to the vector unit.  PAIR: the
 // halves are joined as a register pair, which is what an addition of the result
-// wants (BLAKE2b); SHA-512's results meet only xors and three-term sums, and there
-// the or leaves the scheduler the halves (79 VGPRs next to sha256d, 104 with
-// pairs: six wavefronts per SIMD and four).
+// wants (BLAKE2b, and SHA-512 in a kernel of its own); next to other bodies SHA-512
+// leaves the scheduler the halves (79 VGPRs next to sha256d, 104 with pairs: six
+// wavefronts per SIMD and four).
 template <bool PAIR = false>
 __device__ __forceinline__ uint64_t rotr64(uint64_t x, uint32_t n, bool uni = false) {
   if (uni) return __builtin_rotateright64(x, n);
@@ -63,10 +63,12 @@ __device__ __forceinline__ uint64_t rotr64(uint64_t x, uint32_t n, bool uni = fa
   }
   return PAIR ? pair64(rl, rh) : ((uint64_t)rh << 32) | rl;
 }
+template <bool PAIR = false>
 __device__ __forceinline__ uint64_t shr64(uint64_t x, uint32_t n, bool uni = false) {  // 0 < n < 32
   if (uni) return x >> n;
   const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
-  return ((uint64_t)(hi >> n) << 32) | __builtin_amdgcn_alignbit(hi, lo, n);
+  const uint32_t rl = __builtin_amdgcn_alignbit(hi, lo, n), rh = hi >> n;
+  return PAIR ? pair64(rl, rh) : ((uint64_t)rh << 32) | rl;
 }
 
 // ============================================================ SHA-256d
@@ -362,8 +364,12 @@ struct Sha512 {
   // uniform values (the caller runs them once per wavefront).  The uniform
   // terms of a schedule word are summed first and with the round constant, so
   // that they form one loop-invariant value.
-  // Schedule words below PLAIN keep the plain xors (see the batch kernels).
-  template <int T0, int T1, int PLAIN = 0>
+  // Schedule words below PLAIN keep the plain xors (see the batch kernels).  WIDE:
+  // the big sigmas are one operation each on halves joined as pairs, which
+  // lengthens the live ranges of all rotations (see rotr64): in a kernel of its own
+  // only (61374 walks of a table in the cache at block 1024: 37 us, 38 without; next
+  // to sha256d, split 3 of 4 at block 256 bound to 64 VGPRs, 591 and 592).
+  template <int T0, int T1, int PLAIN = 0, bool WIDE = false>
   __device__ static __forceinline__ void rounds(uint64_t (&v)[8], uint64_t (&w)[16]) {
     uint64_t a = v[0], b = v[1], c = v[2], d = v[3], e = v[4], f = v[5], g = v[6], h = v[7];
 #pragma unroll
@@ -377,8 +383,8 @@ struct Sha512 {
         const int i = t & 15;
         const uint64_t x = w[(i + 1) & 15], y = w[(i + 14) & 15];
         const bool ux = uni(t - 15), uy = uni(t - 2);
-        const uint64_t s0 = xor3(rotr64(x, 1, ux), rotr64(x, 8, ux), shr64(x, 7, ux), ux || t < PLAIN);
-        const uint64_t s1 = xor3(rotr64(y, 19, uy), rotr64(y, 61, uy), shr64(y, 6, uy), uy || t < PLAIN);
+        const uint64_t s0 = xor3(rotr64<WIDE>(x, 1, ux), rotr64<WIDE>(x, 8, ux), shr64<WIDE>(x, 7, ux), ux || t < PLAIN);
+        const uint64_t s1 = xor3(rotr64<WIDE>(y, 19, uy), rotr64<WIDE>(y, 61, uy), shr64<WIDE>(y, 6, uy), uy || t < PLAIN);
         const uint64_t q = w[(i + 9) & 15], r = w[i];
         const bool uq = uni(t - 7), ur = uni(t - 16);
         const uint64_t wu = (uy ? s1 : 0) + (uq ? q : 0) + (ux ? s0 : 0) + (ur ? r : 0);
@@ -386,13 +392,10 @@ struct Sha512 {
         ku = kK[t] + wu;
         w[i] = wu + wv;
       }
-      // S1 and S0 stay plain: as one operation each they lengthen the live ranges
-      // of all rotations (see rotr64) and gain nothing (sha256d and walks, split 3 of
-      // 4 at block 256, bound to 64 VGPRs: 591 us as one, 592 plain)
-      const uint64_t S1 = rotr64(e, 14, us) ^ rotr64(e, 18, us) ^ rotr64(e, 41, us);
+      const uint64_t S1 = xor3(rotr64<WIDE>(e, 14, us), rotr64<WIDE>(e, 18, us), rotr64<WIDE>(e, 41, us), us || !WIDE);
       const uint64_t ch = us ? (e & f) ^ (~e & g) : op3<kCh>(e, f, g);
       const uint64_t T1v = ku + h + S1 + ch + wv;
-      const uint64_t S0 = rotr64(a, 28, us) ^ rotr64(a, 34, us) ^ rotr64(a, 39, us);
+      const uint64_t S0 = xor3(rotr64<WIDE>(a, 28, us), rotr64<WIDE>(a, 34, us), rotr64<WIDE>(a, 39, us), us || !WIDE);
       const uint64_t maj = us ? (a & b) ^ (a & c) ^ (b & c) : op3<kMaj>(a, b, c);
       h = g;
       g = f;
@@ -452,6 +455,7 @@ struct EthashLike {
 
   template <int PLAIN = 0, class Bar>
   __device__ static __forceinline__ void run(const DevTask& dt, const Part& p, Bar&, uint32_t*) {
+    constexpr bool kWide = std::is_same_v<Bar, SoloBarrier>;
     const EthArgs& a = dt.eth;
     if (a.n == 0) return;
     // rounds 0..8 read header words only: uniform, so scalar registers
@@ -485,11 +489,11 @@ struct EthashLike {
 #pragma unroll
         for (int k = 11; k < 15; ++k) w[k] = 0;
         w[15] = 640;
-        Sha512::rounds<9, 16, PLAIN>(v, w);
-        Sha512::rounds<16, 32, PLAIN>(v, w);
-        Sha512::rounds<32, 48, PLAIN>(v, w);
-        Sha512::rounds<48, 64, PLAIN>(v, w);
-        Sha512::rounds<64, 80, PLAIN>(v, w);
+        Sha512::rounds<9, 16, PLAIN, kWide>(v, w);
+        Sha512::rounds<16, 32, PLAIN, kWide>(v, w);
+        Sha512::rounds<32, 48, PLAIN, kWide>(v, w);
+        Sha512::rounds<48, 64, PLAIN, kWide>(v, w);
+        Sha512::rounds<64, 80, PLAIN, kWide>(v, w);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
           const uint64_t hk = Sha512::h0(k) + v[k];

@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(Solo
   __shared__ uint32_t smem[max1(K::lds_words(BLOCK))];
   const Part p{threadIdx.x, (uint32_t)BLOCK, uniform(threadIdx.x >> 6), (uint32_t)(BLOCK / 64),
                blockIdx.x, gridDim.x};
-  WGBarrier bar;
+  SoloBarrier bar;
   K::run(t, p, bar, smem);
 }
 
