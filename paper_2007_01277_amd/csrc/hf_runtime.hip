@@ -603,14 +603,18 @@ uint32_t default_wgs(const hf_task* t, const DevTask& d, int waves, int block, i
     const int64_t enough = std::max<int64_t>(num_cus, (4 * num_cus + waves - 1) / waves);
     need = std::min(need, enough);
   }
-  // arrivals of statistics whose counters share lines (the caller's scratch) are
-  // served one after the other: fewer wavefronts, with four units each or more, have
-  // fewer ([32,16,128,128], caller's scratch, block 512: 77 us on the resident
-  // workgroups, 32)
-  if (t->kind == HF_BN_STATS && d.bn.ctr_shift == 0u && d.bn.C <= 2048u &&
-      !BnStats::whole_channels(d.bn.upc, d.bn.C)) {
-    const int64_t ws = std::min<int64_t>(std::max<int64_t>(d.bn.total / 4u, 8 * num_cus), 16 * num_cus);
-    need = std::min<int64_t>(need, (ws + waves - 1) / waves);
+  // arrivals of statistics are served one after the other on each line of counters:
+  // where those are few (few channels, or the caller's scratch with 32 counters to a
+  // line) fewer wavefronts, with four units each or more, have fewer
+  // ([32,16,128,128], caller's scratch, block 512: 77 us on the resident workgroups,
+  // 32; the library's at block 256: 17.6 and 10.8).  Elsewhere more than 24 per CU
+  // gain nothing ([64,256,56,56] at block 256: 40 us with 28, 37 with 24).
+  if (t->kind == HF_BN_STATS && !BnStats::whole_channels(d.bn.upc, d.bn.C)) {
+    const uint32_t lines = d.bn.ctr_shift ? d.bn.C : (d.bn.C + 31u) / 32u;
+    const int64_t ws =
+        lines > 64u ? 24 * num_cus : std::min<int64_t>(std::max<int64_t>(d.bn.total / 4u, 8 * num_cus), 16 * num_cus);
+    const int64_t wgs = (ws + waves - 1) / waves;
+    need = std::min<int64_t>(need, wgs < num_cus ? wgs : wgs / num_cus * num_cus);
   }
   // (upsample's short units need those gaps covered better still: 12x12 x2 by
   // points, 47 M outputs, block 1024, two workgroups per CU: 64 us in order, 44

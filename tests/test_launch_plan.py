@@ -99,20 +99,27 @@ def test_short_upsample_units_are_taken_several_at_a_time():
         assert P.wgs(t, 16, 1024, 512) <= 512  # their gaps are not covered: resident
 
 
-def test_statistics_with_shared_counter_lines_arrive_less_often():
-    """In the caller's scratch between 8 and 16 wavefronts per CU, four units or more
-    each past that; in the library's own the resident workgroups."""
-    big = (32, 16, 128, 128)
-    for shape in (big, (64, 256, 56, 56), (2, 3, 1024, 1024), (16, 300, 33, 33)):
-        own, mine = P.task(H.HF_BN_STATS, shape), P.task(H.HF_BN_STATS, shape, scratch=True)
-        for block, per_cu in ((256, 7), (512, 3), (1024, 1)):
-            W, res = block // 64, 256 * per_cu
-            g = P.wgs(mine, W, block, res, own=False)
-            assert 1 <= g <= P.wgs(own, W, block, res) and (g - 1) * W < 16 * 256
-            assert g * W >= 8 * 256 or g == P.wgs(own, W, block, res)
-    assert P.wgs(P.task(H.HF_BN_STATS, big), 8, 512, 768) == 768
-    few = P.task(H.HF_BN_STATS, (8, 32, 16, 16), scratch=True)  # whole channels: no counters
-    assert P.wgs(few, 4, 256, 1792, own=False) == P.wgs(few, 4, 256, 1792)
+def test_statistics_with_few_counter_lines_arrive_less_often():
+    """Where arrivals share few lines of counters (the caller's scratch, or up to 64
+    channels) between 8 and 16 wavefronts per CU, four units or more each past that;
+    elsewhere the resident workgroups, up to 24 wavefronts per CU."""
+    few = ((32, 16, 128, 128), (2, 3, 1024, 1024), (64, 64, 112, 112))
+    many = ((64, 256, 56, 56), (16, 300, 33, 33), (256, 2048, 7, 7))
+    for shape in few + many:
+        for own in (True, False):
+            t = P.task(H.HF_BN_STATS, shape, scratch=not own)
+            for block, per_cu in ((256, 7), (512, 3), (1024, 1)):
+                W = block // 64
+                g = P.wgs(t, W, block, 256 * per_cu, own=own)
+                most = min(256 * per_cu, P.useful(t, W))
+                if own and shape in many:
+                    assert g == min(most, 24 * 256 // W)
+                else:
+                    assert 1 <= g <= most and (g - 1) * W < 16 * 256
+                    assert g * W >= 8 * 256 or g == most
+    short = (8, 32, 16, 16)  # whole channels: no counters
+    assert P.wgs(P.task(H.HF_BN_STATS, short, scratch=True), 4, 256, 1792, own=False) == \
+        P.wgs(P.task(H.HF_BN_STATS, short), 4, 256, 1792)
 
 
 @pytest.mark.parametrize("rows", [4099, 1 << 23])
